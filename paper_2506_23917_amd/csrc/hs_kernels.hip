@@ -1194,10 +1194,21 @@ __device__ __forceinline__ void seg_round(double (&x)[K], int head, int tail, do
 // XCD-aware order of the tiles.  Workgroups are dealt to the chip's 8 XCDs in turn (block b
 // runs on XCD b mod 8), and each XCD has its own L2.  Neighbouring tiles read the same source
 // cache lines (a cell's particles come from the cells around it, which belong to tiles a row
-// apart), so each XCD takes whole chunks of kTileChunk consecutive tiles, chunk c going to
-// XCD c mod 8, and its blocks sweep them in order.  The grid is a multiple of 8.
+// apart), so each XCD takes whole chunks of consecutive tiles, chunk c going to XCD c mod 8,
+// and its blocks sweep them in order.  The grid is a multiple of 8.
+// A chunk is 2^chunk_shift tiles: 256 where that gives every XCD at least eight chunks (smaller
+// and larger ones measured slower on the 65k tiles of the 800 x 600 cylinder), else the largest
+// power of two that does, down to single tiles.  With 256 at every size a small batch sat on
+// one or two XCDs: an 18k-particle FP64 tube (75 tiles) took 1183 us a step against 316, the
+// 80 x 60 cylinder (284 tiles) 1399 against 520.
 constexpr int kXcds = 8;
-constexpr int kTileChunk = 256;
+constexpr int kTileChunkShift = 8;
+
+__device__ __forceinline__ int chunk_shift(int ntiles)
+{
+    const int per = ntiles / (8 * kXcds);
+    return per < 1 ? 0 : min(kTileChunkShift, 31 - __clz(per));
+}
 // FP32-mixed tiles of the tile collision kernel with more cells than this send their Step (5)
 // sums in address order (see the kernel); fewer, wider groups send their own.  FP64 tiles always
 // send their own: that kernel runs two waves per SIMD and is bound by instruction issue, its
@@ -1214,11 +1225,10 @@ __device__ __forceinline__ void wave_flush_dtmin(const Ctx &C, int cid, double d
         atomicMin(&C.g->dt_next[cid], (unsigned long long)__double_as_longlong(dtmin));
 }
 
-// Tile of the p-th position in this block's XCD sequence (increasing in p).
-__device__ __forceinline__ int xcd_tile(int p, int xcd)
+// Tile of the p-th position in this block's XCD sequence (increasing in p), chunks of 2^sh.
+__device__ __forceinline__ int xcd_tile(int p, int xcd, int sh)
 {
-    const int chunk = p / kTileChunk;
-    return (chunk * kXcds + xcd) * kTileChunk + (p - chunk * kTileChunk);
+    return ((((p >> sh) * kXcds) + xcd) << sh) + (p & ((1 << sh) - 1));
 }
 
 // Table entries of a tile: first cell, end cell, case.  The tile kernels load those of the
@@ -1277,13 +1287,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(P) ==
     const int NC = C.ncells_total;
 
     const int xcd = blockIdx.x % kXcds, nbx = gridDim.x / kXcds;
+    const int csh = chunk_shift(ntiles);
     int pos = blockIdx.x / kXcds;
-    int t = xcd_tile(pos, xcd);
+    int t = xcd_tile(pos, xcd, csh);
     TileRef nx = tile_ref(C, t, ntiles);
     while (t < ntiles) {
         const TileRef cur = nx;
         pos += nbx;
-        t = xcd_tile(pos, xcd);
+        t = xcd_tile(pos, xcd, csh);
         nx = tile_ref(C, t, ntiles);
         const int cb = cur.cb;
         const int ncl = cur.ce - cb;
@@ -1529,13 +1540,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8))) void
     double dtmin = INFINITY;          // smallest Eq. 25 local step of my_case's cells so far
 
     const int xcd = blockIdx.x % kXcds, nbx = gridDim.x / kXcds;
+    const int csh = chunk_shift(ntiles);
     int pos = blockIdx.x / kXcds;
-    int t = xcd_tile(pos, xcd);
+    int t = xcd_tile(pos, xcd, csh);
     TileRef nx = tile_ref(C, t, ntiles);
     while (t < ntiles) {
         const TileRef cur = nx;
         pos += nbx;
-        t = xcd_tile(pos, xcd);
+        t = xcd_tile(pos, xcd, csh);
         nx = tile_ref(C, t, ntiles);
         const int cb = cur.cb;
         const int ncl = cur.ce - cb;
@@ -1807,13 +1819,14 @@ __device__ __forceinline__ void collide_tile_body(const Ctx &C)
     int my_case = -1;
 
     const int xcd = blockIdx.x % kXcds, nbx = gridDim.x / kXcds;
+    const int csh = chunk_shift(ntiles);
     int pos = blockIdx.x / kXcds;
-    int t = xcd_tile(pos, xcd);
+    int t = xcd_tile(pos, xcd, csh);
     TileRef nx = tile_ref(C, t, ntiles);
     while (t < ntiles) {
         const TileRef cur = nx;
         pos += nbx;
-        t = xcd_tile(pos, xcd);
+        t = xcd_tile(pos, xcd, csh);
         nx = tile_ref(C, t, ntiles);
         const int cb = cur.cb;
         const int ncl = cur.ce - cb;
@@ -3109,8 +3122,7 @@ void Launch::scatter(const Ctx &c, void *s)
     hipLaunchKernelGGL(k_scatter, dim3(grid), dim3(kBlock), 0, S_(s), c);
 }
 // Tile kernels loop over tiles with a fixed grid: wide for the streaming gather and scalar
-// kernels, about the resident capacity for the collision kernel (its per-wave setup and
-// counter flush are paid once per block).
+// kernels; the collision kernel's per-wave setup and counter flush are paid once per block.
 static int tile_grid(const Ctx &c, int which, long long cap)
 {
     long long g = c.grid[which];
@@ -3134,8 +3146,11 @@ void Launch::scalars(const Ctx &c, void *s)
 }
 void Launch::collide(const Ctx &c, void *s)
 {
+    // FP64 tiles differ most in length (its acceptance-rejection draws): 8192 blocks, a tile or
+    // two each, keep the chip even (332 x 249 cylinder, us a step: 745 at 1024 blocks, 600 at
+    // 4096, 550 at 8192 and 16384); FP32 at 4096 (800 x 600 cylinder: 1069; 8192 1091)
     if (c.precision == HS_FP64)
-        hipLaunchKernelGGL(k_collide_tile_f64, dim3(tile_grid(c, HS_KERNEL_COLLIDE, 256ll * 4)), dim3(64), 0, S_(s), c);
+        hipLaunchKernelGGL(k_collide_tile_f64, dim3(tile_grid(c, HS_KERNEL_COLLIDE, 256ll * 32)), dim3(64), 0, S_(s), c);
     else
         hipLaunchKernelGGL(k_collide_tile_f32, dim3(tile_grid(c, HS_KERNEL_COLLIDE, 256ll * 16)), dim3(64), 0, S_(s), c);
 }
