@@ -25,3 +25,33 @@ def test_every_tile_once(gas, ncells):
     scale = np.abs(o["v"]).max()
     assert np.abs(g["vel"] - o["v"]).max() <= 1e-12 * scale
     assert g["acc"][:, 0].sum() == len(g["id"])
+
+
+# queue lengths around a wave's 64 draws, single draws, whole tiles; the last particle of every
+# cell is fast, so the heat flux and with it the number of attempts (up to the cap) is large
+@pytest.mark.parametrize("ncells,ppc", [(1, 3), (1, 33), (1, 64), (1, 65), (1, 192), (2, 100), (60, 3), (21, 8)])
+def test_shakhov_draw_queue(gas, ncells, ppc):
+    from oracle.oracle import Oracle
+    from paper_2506_23917_amd.hs import Sim
+    case = W.relax_0d(ncells=ncells, ppc=ppc)
+    case["dt_over_tau"] = 10.0 ** np.linspace(2, -0.5, ncells)
+    v, cell, ids = W.relax_0d_state(case, ppc=ppc)
+    v[ppc - 1::ppc] *= 30.0
+    ora = Oracle(gas, case, trace=True)
+    ora.set_state(0, None, v, cell, ids, len(ids), 0)
+    cells = ora.get_cells(0)
+    sim = Sim(gas, case, precision="fp64", trace=True, no_particles=True, device="cuda:0")
+    sim.import_state(0, dict(pos=np.zeros((len(ids), 3)), vel=v, cell=cell, id=ids, next_id=len(ids), step=0,
+                             sigc_max=cells["sigc_max"]))
+    attempts = 0
+    for _ in range(4):
+        sim.step(1)
+        ora.step(1)
+        tg, to = sim.trace(0), ora.trace(0)
+        for f in ("n", "ncol", "nacc", "nrelax", "ar_attempts", "ar_cap", "acc_hash"):
+            assert np.array_equal(tg[f], to[f]), f
+        attempts += int((to["ar_attempts"] - to["nrelax"]).sum())
+    assert attempts > 0
+    g, o = sim.export_state(0), ora.get_state(0)
+    assert np.abs(g["vel"] - o["v"]).max() <= 1e-12 * np.abs(o["v"]).max()
+    assert sim.counters(0) == ora.counters(0)
