@@ -1284,9 +1284,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(P) ==
     constexpr int MAXC = TW / 4;
     constexpr int MAXP = TW + D;
     __shared__ __attribute__((aligned(16))) int32_t s_src[MAXP];   // source of each scatter slot
-    __shared__ int32_t s_dsrc[MAXP];      // source of each destination slot
+    __shared__ int32_t s_dsrc[MAXP + 2];  // source of each destination slot; before, the run table
     __shared__ uint8_t s_lc[MAXP];
     __shared__ int32_t c_start[MAXC], c_off[MAXC + 1];
+    __shared__ uint16_t c_run[MAXC];      // first run of each cell
     // first slot of every non-empty cell as a bit, and the cell of each non-empty ordinal:
     // the cell of slot s is s_ord[(non-empty cells starting at or before s) - 1]
     constexpr int RW = (MAXP + 63) / 64;
@@ -1371,26 +1372,92 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(P) ==
                 if (pidx[r] >= 0) s_src[lane + 64 * r] = pidx[r];
         }
         team_sync<64>();
-        // stable order inside each cell: a source's rank among its cell's sources is its
-        // place (sources are distinct); the slots then hold sources in destination order.
-        // The cell's sources are read four at a time (aligned 16-byte LDS reads) and all
-        // counted; the few words of the first and last row outside the cell are counted again
-        // and taken off (words past np are read, added and subtracted alike).
-        static_assert(MAXP % 4 == 0, "whole 16-byte rows");
-        for (int s = lane; s < np; s += 64) {
-            const int lc = s_lc[s];
-            const int o = c_off[lc], e = c_off[lc + 1];
-            const int src = s_src[s];
-            const int u0 = o >> 2, u1 = (e + 3) >> 2;
-            int rk = 0;
-            const int4 *q = reinterpret_cast<const int4 *>(s_src);
-            for (int u = u0; u < u1; ++u) {
-                const int4 w = q[u];
-                rk += (int)(w.x < src) + (int)(w.y < src) + (int)(w.z < src) + (int)(w.w < src);
+        // Stable order inside each cell (the slots then hold sources in destination order).
+        // The move hands out a wave's slots of a cell as one run of increasing sources, all in
+        // one aligned block of 64.  So the slots split into maximal such runs; a run's place is
+        // its cell's start plus the lengths of the cell's runs of lower blocks, found by one lane
+        // per run, and its sources follow in order.  Where two runs of a cell share a block
+        // (particles that k_move_body took, any other slot order) the tile falls back to
+        // counting: a source's rank among its cell's sources is its place.
+        // Counting every source against every other took 292 lane-instructions a particle on the
+        // 800 x 600 cylinder, the runs 158 (kernel 283 -> 271 us: its loads remain), 64 tubes of
+        // 160-particle cells 45 -> 17 us, the FP64 0-D batch (no permutation: no ranks) 39 -> 10.
+        if (!use_perm) {
+            for (int s = lane; s < np; s += 64) s_dsrc[s] = s_src[s];
+        } else {
+            uint16_t *run_at = reinterpret_cast<uint16_t *>(s_dsrc);          // first slot of each run
+            int16_t *run_by = reinterpret_cast<int16_t *>(s_dsrc) + MAXP + 2;  // slots it moves by
+            int rid[R];
+            int nrun = 0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                rid[r] = 0;
+                if (64 * r < np) {
+                    const int s = lane + 64 * r;
+                    bool head = false;
+                    int lc = 0;
+                    if (s < np) {
+                        lc = s_lc[s];
+                        head = s == c_off[lc];
+                        if (!head) {
+                            const int x = s_src[s], y = s_src[s - 1];
+                            head = (x >> 6) != (y >> 6) || x < y;
+                        }
+                    }
+                    const unsigned long long m = __ballot(head);
+                    rid[r] = nrun + __popcll(m & ((2ull << lane) - 1ull)) - 1;
+                    if (head) {
+                        run_at[rid[r]] = (uint16_t)s;
+                        if (s == c_off[lc]) c_run[lc] = (uint16_t)rid[r];
+                    }
+                    nrun += __popcll(m);
+                }
             }
-            for (int k = u0 << 2; k < o; ++k) rk -= (int)(s_src[k] < src);
-            for (int k = e; k < (u1 << 2); ++k) rk -= (int)(s_src[k] < src);
-            s_dsrc[o + rk] = src;
+            if (lane == 0) run_at[nrun] = (uint16_t)np;
+            team_sync<64>();
+            bool tie = false;
+            for (int q = lane; q < nrun; q += 64) {
+                const int at = run_at[q], lc = s_lc[at], e = c_off[lc + 1], blk = s_src[at] >> 6;
+                int to = c_off[lc], a = to;
+                for (int j = c_run[lc]; a < e; ++j) {
+                    const int an = run_at[j + 1], bj = s_src[a] >> 6;
+                    if (bj < blk) to += an - a;
+                    tie = tie || (bj == blk && j != q);
+                    a = an;
+                }
+                run_by[q] = (int16_t)(to - at);
+            }
+            if (!__any(tie)) {
+                team_sync<64>();
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (lane + 64 * r < np) rid[r] = lane + 64 * r + run_by[rid[r]];
+                team_sync<64>();
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (lane + 64 * r < np) s_dsrc[rid[r]] = s_src[lane + 64 * r];
+            } else {
+                team_sync<64>();
+                // the cell's sources are read four at a time (aligned 16-byte LDS reads) and all
+                // counted; the few words of the first and last row outside the cell are counted
+                // again and taken off (words past np are read, added and subtracted alike)
+                static_assert(MAXP % 4 == 0, "whole 16-byte rows");
+                for (int s = lane; s < np; s += 64) {
+                    const int lc = s_lc[s];
+                    const int o = c_off[lc], e = c_off[lc + 1];
+                    const int src = s_src[s];
+                    const int u0 = o >> 2, u1 = (e + 3) >> 2;
+                    int rk = 0;
+                    const int4 *q = reinterpret_cast<const int4 *>(s_src);
+                    for (int u = u0; u < u1; ++u) {
+                        const int4 w = q[u];
+                        rk += (int)(w.x < src) + (int)(w.y < src) + (int)(w.z < src) + (int)(w.w < src);
+                    }
+                    for (int k = u0 << 2; k < o; ++k) rk -= (int)(s_src[k] < src);
+                    for (int k = e; k < (u1 << 2); ++k) rk -= (int)(s_src[k] < src);
+                    s_dsrc[o + rk] = src;
+                }
+            }
         }
         team_sync<64>();
         // gather by destination slot (neighbouring lanes write neighbouring particles and,

@@ -55,3 +55,33 @@ def test_shakhov_draw_queue(gas, ncells, ppc):
     g, o = sim.export_state(0), ora.get_state(0)
     assert np.abs(g["vel"] - o["v"]).max() <= 1e-12 * np.abs(o["v"]).max()
     assert sim.counters(0) == ora.counters(0)
+
+
+# cells of one to many source blocks of 64 and their edges, still particles (one run a cell) to
+# flights over several cells (many short runs)
+@pytest.mark.parametrize("ncells,ppc", [(700, 1), (300, 5), (9, 63), (9, 64), (9, 65), (40, 170)])
+@pytest.mark.parametrize("speed", [0.0, 300.0, 4000.0])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_stable_order_by_runs(gas, ncells, ppc, speed, precision):
+    from paper_2506_23917_amd.hs import Sim
+    rng = np.random.default_rng(ncells * ppc)
+    case = W.sod_1d(ncells=ncells, ppc_left=2)
+    case.update(h=(1.0, 1.0, 1.0), regions=[], F_N=1.0, dt_G=1e-3, capacity=ncells * ppc + 64)
+    m = ncells * ppc
+    cell = np.sort(rng.integers(0, ncells, m).astype(np.int32))
+    pos = np.zeros((m, 3))
+    pos[:, 0] = rng.random(m)
+    vel = np.zeros((m, 3))
+    vel[:, 0] = speed * rng.standard_normal(m)
+    ids = rng.permutation(m).astype(np.int64)
+    sim = Sim(gas, case, precision=precision, no_particles=True, device="cuda:0")
+    sim.import_state(0, dict(pos=pos, vel=vel, cell=cell, id=ids, next_id=m, step=0,
+                             sigc_max=np.full(ncells, 1e-16)))
+    for _ in range(2):
+        before = sim.export_state(0)
+        sim.step(1)
+        after = sim.export_state(0)
+        # the cells the particles went to, then the stable order of the particles before the step
+        where = dict(zip(after["id"], after["cell"]))
+        new = np.array([where[i] for i in before["id"]])
+        assert np.array_equal(after["id"], before["id"][np.argsort(new, kind="stable")])
