@@ -37,8 +37,11 @@ __device__ __forceinline__ W4 philox10(uint32_t c0, uint32_t c1, uint32_t c2, ui
         const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
         const uint32_t h0 = (uint32_t)(p0 >> 32), l0 = (uint32_t)p0;
         const uint32_t h1 = (uint32_t)(p1 >> 32), l1 = (uint32_t)p1;
-        const uint32_t n0 = h1 ^ c1 ^ k0;
-        const uint32_t n2 = h0 ^ c3 ^ k1;
+        // three-way xor as one instruction (truth table 0x96): the compiler xors with the uniform
+        // key apart, two instructions a word (steps: 800 x 600 cylinder 1052 -> 1038 us, 96 x 64
+        // x 64 sphere 1050 -> 966, three O-grids 476 -> 461)
+        const uint32_t n0 = __builtin_amdgcn_bitop3_b32(h1, c1, k0, 0x96);
+        const uint32_t n2 = __builtin_amdgcn_bitop3_b32(h0, c3, k1, 0x96);
         c0 = n0;
         c1 = l1;
         c2 = n2;
