@@ -3445,6 +3445,25 @@ void launch_finalize(const Ctx &c, void *s, int case_id, int ncells, double *out
     hipLaunchKernelGGL(k_finalize, dim3(blocks_for(ncells, 256)), dim3(256), 0, S_(s), c, case_id, out);
 }
 
+// Whether work of two streams can overlap: the first stream's kernel holds its queue for about
+// kHoldTicks of the 100 MHz wall clock and stamps its end, the second stream's stamps its start.
+constexpr unsigned long long kHoldTicks = 3000;
+
+__global__ void k_queue_hold(unsigned long long *t)
+{
+    const unsigned long long t0 = wall_clock64();
+    for (int k = 0; k < 20000 && wall_clock64() - t0 < kHoldTicks; ++k) __builtin_amdgcn_s_sleep(4);
+    t[0] = wall_clock64();
+}
+
+__global__ void k_queue_stamp(unsigned long long *t) { t[1] = wall_clock64(); }
+
+void launch_queue_probe(void *first, void *second, unsigned long long *t)
+{
+    hipLaunchKernelGGL(k_queue_hold, dim3(1), dim3(1), 0, S_(first), t);
+    hipLaunchKernelGGL(k_queue_stamp, dim3(1), dim3(1), 0, S_(second), t);
+}
+
 // Fixed scratch array for hs_init_particles_static (sims whose callers cannot allocate device
 // memory).  Every device holds its own copy; its address is looked up once per device, with
 // that device current, and kept: host code uses only that address, never the array's name.

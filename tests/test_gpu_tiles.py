@@ -85,3 +85,19 @@ def test_stable_order_by_runs(gas, ncells, ppc, speed, precision):
         where = dict(zip(after["id"], after["cell"]))
         new = np.array([where[i] for i in before["id"]])
         assert np.array_equal(after["id"], before["id"][np.argsort(new, kind="stable")])
+
+
+# sims made one after the other and alive together (each picks its side stream), and one replaying
+# a graph, whose dense cells run beside the tiles
+@pytest.mark.parametrize("n", [1, 6])
+def test_sims_side_by_side(gas, n):
+    from paper_2506_23917_amd.hs import Sim
+    case = W.sod_1d(ncells=40, ppc_left=600, n_steady=0)
+    sims = [Sim(gas, case, precision="fp64", device="cuda:0", graph=k == 5) for k in range(n + 1)]
+    for s in sims:
+        s.step(4)
+    first = sims[0].export_state(0)
+    for s in sims[1:]:
+        st = s.export_state(0)
+        assert np.array_equal(st["id"], first["id"]) and np.array_equal(st["vel"], first["vel"])
+        assert np.array_equal(st["acc"], first["acc"])
