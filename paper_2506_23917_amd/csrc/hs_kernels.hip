@@ -34,16 +34,121 @@ __device__ __forceinline__ void team_sync()
     }
 }
 
+// ---- lane exchange inside a wave, all on the vector ALU (every lane active): DPP patterns
+// within a row of 16 lanes, the permlane swaps between rows.  The LDS-pipe shuffles they replace
+// cost an address computation and about a hundred clocks each, in chains of six per reduction.
+// Steps with shuffles and without (and the tile kernel's lane groups laid out from ballots): three
+// O-grids 461 -> 445 us, FP64 332 x 249 cylinder 416 -> 402, 800 x 600 1038 -> 1016, 64 tubes
+// 214 -> 205.
+
+template <int CTRL>
+__device__ __forceinline__ int dpp_partner_i(int x)
+{
+    return __builtin_amdgcn_mov_dpp(x, CTRL, 0xF, 0xF, true);
+}
+// Value held by the partner lane under a DPP lane pattern.
+template <int CTRL>
+__device__ __forceinline__ double dpp_partner(double x)
+{
+    const long long b = __double_as_longlong(x);
+    return __longlong_as_double(((long long)dpp_partner_i<CTRL>((int)(b >> 32)) << 32) |
+                                (long long)(unsigned int)dpp_partner_i<CTRL>((int)b));
+}
+template <int CTRL>
+__device__ __forceinline__ long long dpp_partner_l(long long b)
+{
+    return ((long long)dpp_partner_i<CTRL>((int)(b >> 32)) << 32) | (long long)(unsigned int)dpp_partner_i<CTRL>((int)b);
+}
+// DPP lane patterns: the other lane of a pair, the other pair of a quad (quad_perm), the other
+// quad of an 8-lane half row (half-row mirror), the other half of a 16-lane row (row mirror); row
+// rotations by 4 and 8 lanes.
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
+constexpr int kDppRor4 = 0x124, kDppRor8 = 0x128;
+
+// The two values of every pair of lanes 16 (32) apart, the lower lane's first, in both lanes.
+struct PairI {
+    int a, b;
+};
+template <int APART>
+__device__ __forceinline__ PairI row_pair(int x)
+{
+    static_assert(APART == 16 || APART == 32, "rows of 16 lanes");
+    if constexpr (APART == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap((unsigned int)x, (unsigned int)x, false, false);
+        return {(int)r[0], (int)r[1]};
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap((unsigned int)x, (unsigned int)x, false, false);
+        return {(int)r[0], (int)r[1]};
+    }
+}
+template <int APART>
+__device__ __forceinline__ double row_pair_sum(double x)
+{
+    const long long v = __double_as_longlong(x);
+    const PairI lo = row_pair<APART>((int)v), hi = row_pair<APART>((int)(v >> 32));
+    return __longlong_as_double(((long long)hi.a << 32) | (long long)(unsigned int)lo.a) +
+           __longlong_as_double(((long long)hi.b << 32) | (long long)(unsigned int)lo.b);
+}
+template <int APART>
+__device__ __forceinline__ long long row_pair_sum_l(long long v)
+{
+    const PairI lo = row_pair<APART>((int)v), hi = row_pair<APART>((int)(v >> 32));
+    return (((long long)hi.a << 32) | (long long)(unsigned int)lo.a) + (((long long)hi.b << 32) | (long long)(unsigned int)lo.b);
+}
+
+// Butterfly sum over the wave, partners 32, 16, .. 1 lanes apart: every lane ends with the same
+// bits.  (After the levels 32, 16 and 8 a lane's value depends on its place in the half row only,
+// so the rotation by 4 brings the value of the lane 4 apart.)
+__device__ __forceinline__ double wave_sum(double x)
+{
+    x = row_pair_sum<32>(x);
+    x = row_pair_sum<16>(x);
+    x = x + dpp_partner<kDppRor8>(x);
+    x = x + dpp_partner<kDppRor4>(x);
+    x = x + dpp_partner<kDppXor2>(x);
+    return x + dpp_partner<kDppXor1>(x);
+}
+__device__ __forceinline__ long long wave_sum_l(long long x)
+{
+    x = row_pair_sum_l<32>(x);
+    x = row_pair_sum_l<16>(x);
+    x += dpp_partner_l<kDppRor8>(x);
+    x += dpp_partner_l<kDppRor4>(x);
+    x += dpp_partner_l<kDppXor2>(x);
+    return x + dpp_partner_l<kDppXor1>(x);
+}
+__device__ __forceinline__ int wave_max(int x)
+{
+    PairI p = row_pair<32>(x);
+    p = row_pair<16>(max(p.a, p.b));
+    x = max(p.a, p.b);
+    x = max(x, dpp_partner_i<kDppRor8>(x));
+    x = max(x, dpp_partner_i<kDppRor4>(x));
+    x = max(x, dpp_partner_i<kDppXor2>(x));
+    return __builtin_amdgcn_readfirstlane(max(x, dpp_partner_i<kDppXor1>(x)));
+}
+
+// Inclusive prefix sum over the wave: row shifts, then each row's last value broadcast on.
+__device__ __forceinline__ int wave_incl_scan(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr 1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // lane 15 to row 1, 47 to 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // lane 31 to rows 2 and 3
+    return v;
+}
+// The wave's total of such a prefix sum (uniform).
+__device__ __forceinline__ int wave_last(int incl) { return __builtin_amdgcn_readlane(incl, 63); }
+
 // Sum K doubles over the team; every thread ends with the same bits (butterfly adds are
 // commutative pairwise, the cross-wave step uses one fixed order).
 template <int TEAM, int K>
 __device__ __forceinline__ void team_sum(double (&v)[K], double *red)
 {
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v[k] = v[k] + __shfl_xor(v[k], off, 64);
-    }
+    for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
     if constexpr (TEAM > 64) {
         const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
         __syncthreads();
@@ -61,47 +166,6 @@ __device__ __forceinline__ void team_sum(double (&v)[K], double *red)
     }
 }
 
-template <int TEAM, int K>
-__device__ __forceinline__ void team_sum_i(long long (&v)[K], long long *red)
-{
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
-    }
-    if constexpr (TEAM > 64) {
-        const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-        __syncthreads();
-        if (lane == 0) {
-#pragma unroll
-            for (int k = 0; k < K; ++k) red[w * K + k] = v[k];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            long long s = 0;
-            for (int ww = 0; ww < TEAM / 64; ++ww) s += red[ww * K + k];
-            v[k] = s;
-        }
-    }
-}
-
-template <int TEAM>
-__device__ __forceinline__ bool team_any(bool p, int *redi)
-{
-    const bool w = __any(p);
-    if constexpr (TEAM == 64) {
-        return w;
-    } else {
-        __syncthreads();
-        if (threadIdx.x == 0) redi[0] = 0;
-        __syncthreads();
-        if (w && (threadIdx.x & 63) == 0) atomicOr(&redi[0], 1);
-        __syncthreads();
-        return redi[0] != 0;
-    }
-}
-
 // Add `val` to base[key] for every active lane, one atomic per distinct key in the wave.
 __device__ __forceinline__ void wave_add(long long *base, int stride, int key, int idx, long long val, bool active)
 {
@@ -110,9 +174,7 @@ __device__ __forceinline__ void wave_add(long long *base, int stride, int key, i
         const int leader = __ffsll((long long)pending) - 1;
         const int k0 = __shfl(key, leader, 64);
         const bool mine = ((pending >> (threadIdx.x & 63)) & 1ull) && key == k0;
-        long long s = mine ? val : 0;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+        const long long s = wave_sum_l(mine ? val : 0);
         if ((threadIdx.x & 63) == leader) atomicAdd((unsigned long long *)&base[(long long)k0 * stride + idx], (unsigned long long)s);
         pending &= ~__ballot(mine);
     }
@@ -413,12 +475,7 @@ constexpr int kScanTile = kBlock * kScanItems;
 __device__ __forceinline__ int block_excl_scan(int v, int *lds, int &total)
 {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int incl = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int y = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += y;
-    }
+    const int incl = wave_incl_scan(v);
     __syncthreads();
     if (lane == 63) lds[w] = incl;
     __syncthreads();
@@ -805,9 +862,7 @@ __device__ __forceinline__ void tally_add(const Ctx &C, CaseTally &T, int cid, i
     bool any = false;
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-        long long x = v[j];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+        const long long x = wave_sum_l(v[j]);
         tot[j] = x;
         any = any || x != 0;
     }
@@ -1170,44 +1225,6 @@ __device__ __forceinline__ void wave_flush_counts(const Ctx &C, int cid, CellCou
 
 // ---- wavefront-tile collide kernel ----------------------------------------------------
 
-// Inclusive prefix sum over the wavefront.
-__device__ __forceinline__ int wave_incl_scan(int v)
-{
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int y = __shfl_up(v, off, 64);
-        if (lane >= off) v += y;
-    }
-    return v;
-}
-
-// One round of segmented sums: lane holds K values of slot base + lane; `head` is the first
-// lane of that slot's cell within the round (cells are contiguous runs of slots).  After
-// the segmented scan, the owner lane of each cell pulls its run's sum from `tail` (the last
-// lane of its run in this round, or -1) and adds it to acc.  The order of additions is
-// fixed, so results are reproducible.
-template <int K>
-__device__ __forceinline__ void seg_round(double (&x)[K], int head, int tail, double (&acc)[K])
-{
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const bool take = lane - off >= head;
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const double y = __shfl_up(x[k], off, 64);
-            if (take) x[k] = x[k] + y;
-        }
-    }
-    const int src = tail >= 0 ? tail : lane;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const double y = __shfl(x[k], src, 64);
-        if (tail >= 0) acc[k] = acc[k] + y;
-    }
-}
-
 // XCD-aware order of the tiles.  Workgroups are dealt to the chip's 8 XCDs in turn (block b
 // runs on XCD b mod 8), and each XCD has its own L2.  Neighbouring tiles read the same source
 // cache lines (a cell's particles come from the cells around it, which belong to tiles a row
@@ -1335,7 +1352,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(P) ==
         const int nn = (own && !dense) ? n : 0;
         const int incl = wave_incl_scan(nn);
         const int off = incl - nn;
-        const int np = __shfl(incl, 63, 64);
+        const int np = wave_last(incl);
         if (own) c_off[lane] = off;
         if (lane == 0) c_off[ncl] = np;
         if (lane < RW) s_first[lane] = 0ull;
@@ -1503,28 +1520,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(P) ==
     }
 }
 
-// Value held by the partner lane under a DPP lane pattern (every lane active).
-template <int CTRL>
-__device__ __forceinline__ double dpp_partner(double x)
-{
-    const long long b = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
-    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned int)lo);
-}
-template <int CTRL>
-__device__ __forceinline__ int dpp_partner_i(int x)
-{
-    return __builtin_amdgcn_mov_dpp(x, CTRL, 0xF, 0xF, true);
-}
-// DPP lane patterns: the other lane of a pair, the other pair of a quad (quad_perm), the other
-// quad of an 8-lane half row (half-row mirror), the other half of a 16-lane row (row mirror).
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
-
 // Butterfly sum over each aligned group of 2^kb lanes (kb uniform in the wave).  Every lane
 // of a group ends with the same bits: at each level the two partners add the same two values
 // (partial sums of complementary halves).  Levels within a 16-lane row move data with DPP,
-// the two wider ones with cross-lane shuffles.
+// the two wider ones with the row swaps.
 template <int K>
 __device__ __forceinline__ void group_sum(double (&x)[K], int kb)
 {
@@ -1544,9 +1543,13 @@ __device__ __forceinline__ void group_sum(double (&x)[K], int kb)
 #pragma unroll
         for (int k = 0; k < K; ++k) x[k] = x[k] + dpp_partner<kDppMirror>(x[k]);
     }
-    for (int m = 16; m < (1 << kb); m <<= 1) {
+    if (kb >= 5) {
 #pragma unroll
-        for (int k = 0; k < K; ++k) x[k] = x[k] + __shfl_xor(x[k], m, 64);
+        for (int k = 0; k < K; ++k) x[k] = row_pair_sum<16>(x[k]);
+    }
+    if (kb >= 6) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) x[k] = row_pair_sum<32>(x[k]);
     }
 }
 
@@ -1556,7 +1559,8 @@ __device__ __forceinline__ int group_sum_i(int x, int kb)
     if (kb >= 2) x += dpp_partner_i<kDppXor2>(x);
     if (kb >= 3) x += dpp_partner_i<kDppHalfMirror>(x);
     if (kb >= 4) x += dpp_partner_i<kDppMirror>(x);
-    for (int m = 16; m < (1 << kb); m <<= 1) x += __shfl_xor(x, m, 64);
+    if (kb >= 5) { const PairI p = row_pair<16>(x); x = p.a + p.b; }
+    if (kb >= 6) { const PairI p = row_pair<32>(x); x = p.a + p.b; }
     return x;
 }
 
@@ -1582,9 +1586,13 @@ __device__ __forceinline__ void group_sum_v(double (&x)[K], int kb, int kbmax)
 #pragma unroll
         for (int k = 0; k < K; ++k) { const double y = dpp_partner<kDppMirror>(x[k]); if (kb >= 4) x[k] = x[k] + y; }
     }
-    for (int l = 4; l < kbmax; ++l) {
+    if (kbmax >= 5) {
 #pragma unroll
-        for (int k = 0; k < K; ++k) { const double y = __shfl_xor(x[k], 1 << l, 64); if (kb > l) x[k] = x[k] + y; }
+        for (int k = 0; k < K; ++k) { const double y = row_pair_sum<16>(x[k]); if (kb >= 5) x[k] = y; }
+    }
+    if (kbmax >= 6) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) { const double y = row_pair_sum<32>(x[k]); if (kb >= 6) x[k] = y; }
     }
 }
 
@@ -1594,7 +1602,8 @@ __device__ __forceinline__ int group_sum_iv(int x, int kb, int kbmax)
     if (kbmax >= 2) { const int y = dpp_partner_i<kDppXor2>(x); if (kb >= 2) x += y; }
     if (kbmax >= 3) { const int y = dpp_partner_i<kDppHalfMirror>(x); if (kb >= 3) x += y; }
     if (kbmax >= 4) { const int y = dpp_partner_i<kDppMirror>(x); if (kb >= 4) x += y; }
-    for (int l = 4; l < kbmax; ++l) { const int y = __shfl_xor(x, 1 << l, 64); if (kb > l) x += y; }
+    if (kbmax >= 5) { const PairI p = row_pair<16>(x); if (kb >= 5) x = p.a + p.b; }
+    if (kbmax >= 6) { const PairI p = row_pair<32>(x); if (kb >= 6) x = p.a + p.b; }
     return x;
 }
 
@@ -1887,8 +1896,8 @@ __device__ __forceinline__ void collide_tile_body(const Ctx &C)
     using UWord = std::conditional_t<sizeof(P) == 8, unsigned long long, unsigned int>;
     __shared__ UWord c_obs[MAXC], c_hash[MAXC];
     __shared__ int32_t c_nacc[MAXC];
-    __shared__ uint8_t c_goff[MAXC], c_gkb[MAXC];
-    __shared__ uint8_t s_gcell[64];       // tile-local cell of each lane's group (0xFF: none)
+    __shared__ uint8_t c_goff[MAXC];
+    __shared__ uint8_t s_gcell[64];       // tile-local cell of the group starting at each lane
     Globals *G = C.g;
     if (G->halt) return;
     const int lane = threadIdx.x;
@@ -1946,12 +1955,12 @@ __device__ __forceinline__ void collide_tile_body(const Ctx &C)
             nn0 = n_lane > D ? 0 : n_lane;
         }
         const int incl = wave_incl_scan(nn0);
-        const int np = __shfl(incl, 63, 64);
+        const int np = wave_last(incl);
         if (np == 0) continue;           // empty cells only (or dense ones, served elsewhere)
         // without a dense cell the tile's slots are the contiguous run of the sorted state that
         // starts at its first cell (nearly every tile); else a slot's cell is searched for
         const bool contig = !__any(lane < ncl && n_lane > D);
-        const int base0 = __shfl(start_l, 0, 64);
+        const int base0 = __builtin_amdgcn_readfirstlane(start_l);
         if (lane < ncl) c_off[lane] = incl - nn0;
         if (lane == 0) c_off[ncl] = np;
         team_sync<64>();
@@ -2023,49 +2032,56 @@ __device__ __forceinline__ void collide_tile_body(const Ctx &C)
         // ---- lane groups sized to the work: a cell with nn particles of the tile's np gets an
         // aligned group of 2^kb ~ 64 nn / np lanes (one at least if nn > 0, none for an empty
         // or dense cell); groups are laid out largest first, which aligns each to its size
-        int gsz = 0;
-        if (lane < ncl) {
-            const int nnc = c_off[lane + 1] - c_off[lane];
-            if (nnc > 0) gsz = 1 << (31 - __clz(max(1, (64 * nnc) / np)));
-        }
-        for (;;) {                        // fit into 64 lanes: halve the largest group
-            int tot = gsz, mx = gsz;
+        int gl = -1;                      // log2 of the cell's group size
+        if (nn0 > 0) gl = 31 - __clz(max(1, (64 * nn0) / np));
+        unsigned long long cls[7];        // the cells (lanes) of each group size, uniform
+        int tot = 0;
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-                tot += __shfl_xor(tot, off, 64);
-                mx = max(mx, __shfl_xor(mx, off, 64));
-            }
-            if (tot <= 64) break;
-            const unsigned long long m = __ballot(gsz == mx);
-            if (lane == __ffsll((long long)m) - 1) gsz >>= 1;
+        for (int l = 0; l < 7; ++l) {
+            cls[l] = __ballot(gl == l);
+            tot += __popcll(cls[l]) << l;
         }
+        // fit into 64 lanes: halve the largest group, the lowest cell's first
+#pragma unroll
+        for (int l = 6; l > 0; --l) {
+            while (tot > 64 && cls[l]) {
+                const unsigned long long first = cls[l] & -cls[l];
+                cls[l] ^= first;
+                cls[l - 1] |= first;
+                tot -= 1 << (l - 1);
+            }
+        }
+        // lanes of each size class in turn: the cell lanes take their group's first lane, every
+        // lane finds the first lane of its own group
+        int goff = 0xFF, g0 = 0, kb = 0, kbmax = 0;
+        bool own = false;
         {
-            int goff = 0, gbase = 0;
-            for (int sz = 64; sz >= 1; sz >>= 1) {
-                const unsigned long long m = __ballot(gsz == sz);
-                if (gsz == sz) goff = gbase + __popcll(m & ((1ull << lane) - 1ull)) * sz;
-                gbase += __popcll(m) * sz;
-            }
-            s_gcell[lane] = 0xFF;
-            team_sync<64>();
-            for (int j = 0; j < gsz; ++j) s_gcell[goff + j] = (uint8_t)lane;
-            if (lane < ncl) {
-                c_goff[lane] = (uint8_t)(gsz > 0 ? goff : 0xFF);   // 0xFF: no group
-                c_gkb[lane] = (uint8_t)(gsz > 0 ? 31 - __clz(gsz) : 0);
-                c_kb[lane] = 0;
-            }
-            team_sync<64>();
-        }
-        const int gcell = s_gcell[lane];
-        const bool own = gcell != 0xFF;
-        const int gc = own ? gcell : 0;
-        const int kb = own ? (int)c_gkb[gc] : 0;
-        const int kk = 1 << kb;
-        const int sub = own ? lane - (int)c_goff[gc] : 0;
-        const int g = cb + gc;
-        int kbmax = kb;
+            const unsigned long long below = (1ull << lane) - 1ull;
+            int base = 0;
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) kbmax = max(kbmax, __shfl_xor(kbmax, off, 64));
+            for (int l = 6; l >= 0; --l) {
+                const int cnt = __popcll(cls[l]);
+                if ((cls[l] >> lane) & 1ull) goff = base + (__popcll(cls[l] & below) << l);
+                const int r = lane - base;
+                if (r >= 0 && r < (cnt << l)) {
+                    own = true;
+                    kb = l;
+                    g0 = base + ((r >> l) << l);
+                }
+                if (cnt && kbmax < l) kbmax = l;
+                base += cnt << l;
+            }
+        }
+        if (goff != 0xFF) s_gcell[goff] = (uint8_t)lane;
+        if (lane < ncl) {
+            c_goff[lane] = (uint8_t)goff;                              // 0xFF: no group
+            c_kb[lane] = 0;
+        }
+        team_sync<64>();
+        const int gc = own ? (int)s_gcell[g0] : 0;
+        const int kk = 1 << kb;
+        const int sub = own ? lane - g0 : 0;
+        const int g = cb + gc;
         double scmax = 0.0, U[3] = {0.0, 0.0, 0.0}, T = 0.0, pr = 0.0;
         int ncol = 0;
         bool active = false;
@@ -2103,7 +2119,7 @@ __device__ __forceinline__ void collide_tile_body(const Ctx &C)
         team_sync<64>();
         const int nc_l = lane < ncl ? c_kb[lane] : 0;
         const int kincl = wave_incl_scan(nc_l);
-        const int kall = __shfl(kincl, 63, 64);
+        const int kall = wave_last(kincl);
         team_sync<64>();
         if (lane < ncl) c_kb[lane] = kincl - nc_l;
         if (lane == 0) c_kb[ncl] = kall;
@@ -2249,9 +2265,7 @@ __device__ __forceinline__ void collide_tile_body(const Ctx &C)
             }
             const uint32_t *ids = Dd.id + c_start[gc];
             const int mine = pr > 0.0 ? (nn - sub + kk - 1) >> kb : 0;   // particles of this lane
-            int most = mine;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) most = max(most, __shfl_xor(most, off, 64));
+            const int most = wave_max(mine);
             int m = 0;                     // draws queued (uniform)
 #pragma unroll 1
             for (int k0 = 0; k0 < most; k0 += 4) {
