@@ -1177,18 +1177,6 @@ __device__ __forceinline__ bool shakhov_try(uint32_t sd0, uint32_t sd1, int64_t 
     return A / am > Real<P>::uni(w5.x);
 }
 
-// The whole draw, attempt after attempt: the attempts used, negative if none was accepted (the
-// last draw then stands).
-template <typename P>
-__device__ __forceinline__ int shakhov_draw(uint32_t sd0, uint32_t sd1, int64_t id, uint32_t st, const P *par,
-                                            P one_m_pr, P Cv[3])
-{
-#pragma unroll 1
-    for (int a = 0; a < kMaxShakhov; ++a)
-        if (shakhov_try<P>(sd0, sd1, id, st, (uint32_t)a, par, one_m_pr, Cv)) return a + 1;
-    return -kMaxShakhov;
-}
-
 // Lanes per queued draw of a batch of n <= 64 draws, as a power of two: the wave's lanes are
 // shared out evenly, so the last draws of a queue try several of their attempts at once.
 __device__ __forceinline__ int draw_lanes_log2(int n)
@@ -2533,19 +2521,23 @@ __device__ __forceinline__ void bitonic_sort(int32_t *a, int p2, int tid)
 // lists of its classes only; results do not depend on the class.
 
 template <typename P, int CAPB, int NB, bool GLOB = false>
-__global__ __launch_bounds__(NB) void k_collide_dense(Ctx C, int cls_lo, int cls_hi)
+__global__ __launch_bounds__(NB) __attribute__((amdgpu_waves_per_eu(sizeof(P) == 4 && CAPB <= kCapBlockMax ? 4 : 1, 8))) void k_collide_dense(Ctx C, int cls_lo, int cls_hi)
 {
     constexpr int KC = 2 * NB;             // NTC candidates per chunk (two per thread)
     static_assert(KC <= 1024, "candidate number fits the claim word");
     constexpr int CAPL = GLOB ? 4 : CAPB;  // LDS rows (the global class keeps its cell in memory)
     __shared__ __attribute__((aligned(16))) int32_t s_src[CAPL];   // sources during the gather, then claim words
-    __shared__ P s_v[3][CAPL];
+    __shared__ __attribute__((aligned(16))) P s_v[3][CAPL];
     __shared__ double s_red[(NB / 64) * 12];
     __shared__ unsigned long long s_obs, s_hash;
     __shared__ int s_nacc, s_left;
     __shared__ int32_t s_rel[3];
-    __shared__ int s_rows[8];                  // runs starting in each row of 64 slots (ranking)
+    __shared__ int s_rows[64];                 // runs starting in each row of 64 slots (ranking)
     uint32_t *s_claim = (uint32_t *)s_src;
+    // Shakhov queue of one wave: its particles of a cell in LDS, chunks of a cell of the global class
+    constexpr int kSlotBits = 13, kQueue = (GLOB ? kCapBlockMax : CAPB) / (NB / 64);
+    static_assert(kQueue % 64 == 0 && kQueue * (NB / 64) <= (1 << kSlotBits), "queue word holds the particle");
+    __shared__ uint32_t s_queue[GLOB ? kCapBlockMax : 1];
     Globals *G = C.g;
     if (G->halt) return;
     const int tid = threadIdx.x;
@@ -2602,28 +2594,19 @@ __global__ __launch_bounds__(NB) void k_collide_dense(Ctx C, int cls_lo, int cls
                 srt[rk] = src;
             }
         }
-        // up to kRankMax particles: each source's rank among the cell's (sources are distinct)
-        // from its runs: the slots split into maximal runs of increasing sources inside one
-        // aligned block of 64 source indices (the move hands out a wave's slots of a cell as one
-        // such run).  Runs of different blocks are ordered by their block, so a source's rank is
-        // the length of the runs of lower blocks plus, in each run of its own block (its own
-        // run, rarely another), the sources below it (binary search).  Run starts and blocks go
-        // to the first two velocity rows and the sorted sources to the third, all free until
-        // the gather.  Denser cells: bitonic sort in place.
-        constexpr int kRankMax = CAPB < 512 ? CAPB : 512;
-        constexpr int GRK = (kRankMax + NB - 1) / NB;
-        static_assert(kRankMax / 64 <= 8, "run counts of the rows fit");
-        const bool by_rank = !GLOB && use_perm && n <= kRankMax;
-        int rsrc[GRK];
+        // Stable order by runs, as in k_sort_gather: a run's place is the length of the cell's runs
+        // of lower source blocks, found by one thread per run (four runs a read), and its sources
+        // follow in order.  Cells where two runs share a block (particles that k_move_body took)
+        // are sorted bitonically.  (Three O-grids, 330 particles a cell: step 445 us with a search of
+        // all runs for every source, 406 so and with the draw queue below.)
         if constexpr (!GLOB) {
-            int p2 = 4;
-            while (p2 < n) p2 <<= 1;
-            for (int k = tid; k < p2; k += NB) s_src[k] = k < n ? (use_perm ? C.perm[s0 + k] : s0 + k) : 0x7fffffff;
+            for (int k = tid; k < n; k += NB) s_src[k] = use_perm ? C.perm[s0 + k] : s0 + k;
             __syncthreads();
-            if (by_rank) {
-                int32_t *run_at = reinterpret_cast<int32_t *>(&s_v[0][0]);
-                int32_t *run_blk = reinterpret_cast<int32_t *>(&s_v[1][0]);
-                int32_t *rk_out = reinterpret_cast<int32_t *>(&s_v[2][0]);
+            if (use_perm) {
+                int32_t *len = reinterpret_cast<int32_t *>(&s_v[0][0]);   // length and block of each
+                int32_t *blk = reinterpret_cast<int32_t *>(&s_v[1][0]);   // run; then the sorted sources
+                int32_t *at = reinterpret_cast<int32_t *>(&s_v[2][0]);    // its first slot; then how
+                                                                          // far its slots move
                 const int lane = tid & 63, nrow = (n + 63) >> 6;
                 auto run_head = [&](int k) {
                     if (k >= n) return false;
@@ -2636,50 +2619,50 @@ __global__ __launch_bounds__(NB) void k_collide_dense(Ctx C, int cls_lo, int cls
                     if (lane == 0) s_rows[r] = __popcll(m);
                 }
                 __syncthreads();
-                int nrun = 0;
-                for (int r = 0; r < nrow; ++r) nrun += s_rows[r];
+                const int rows = lane < nrow ? s_rows[lane] : 0;
+                const int upto = wave_incl_scan(rows);
+                const int nrun = wave_last(upto);
                 for (int r = tid >> 6; r < nrow; r += NB / 64) {
-                    int before = 0;
-                    for (int q = 0; q < r; ++q) before += s_rows[q];
                     const int k = 64 * r + lane;
                     const bool h = run_head(k);
                     const unsigned long long m = __ballot(h);
-                    if (h) {
-                        const int j = before + __popcll(m & ((1ull << lane) - 1ull));
-                        run_at[j] = k;
-                        run_blk[j] = s_src[k] >> 6;
-                    }
-                }
-                if (tid == 0) run_at[nrun] = n;
-                __syncthreads();
-                for (int k = tid; k < n; k += NB) {
-                    const int x = s_src[k], bx = x >> 6;
-                    int rk = 0;
-                    for (int j = 0; j < nrun; ++j) {
-                        const int bj = run_blk[j], a = run_at[j], e = run_at[j + 1];
-                        if (bj < bx) {
-                            rk += e - a;
-                        } else if (bj == bx) {
-                            int lo = a, hi = e;            // first source of the run not below x
-                            while (lo < hi) {
-                                const int mid = (lo + hi) >> 1;
-                                if (s_src[mid] < x) lo = mid + 1;
-                                else hi = mid;
-                            }
-                            rk += lo - a;
-                        }
-                    }
-                    rk_out[rk] = x;
+                    if (h) at[__builtin_amdgcn_readlane(upto - rows, r) + __popcll(m & ((1ull << lane) - 1ull))] = k;
                 }
                 __syncthreads();
-                // every thread takes its sources before any velocity row is written
-#pragma unroll
-                for (int r = 0; r < GRK; ++r) {
-                    const int k = tid + NB * r;
-                    rsrc[r] = k < n ? rk_out[k] : 0;
+                for (int q = tid; q < ((nrun + 3) & ~3); q += NB) {
+                    len[q] = q < nrun ? (q + 1 < nrun ? at[q + 1] : n) - at[q] : 0;
+                    blk[q] = q < nrun ? s_src[at[q]] >> 6 : 0x7fffffff;
                 }
-            } else if (use_perm) {
-                bitonic_sort<NB>(s_src, p2, tid);
+                __syncthreads();
+                bool tie = false;
+                for (int q = tid; q < nrun; q += NB) {
+                    const int mine = blk[q];
+                    int to = 0, same = 0;
+                    for (int j = 0; j < nrun; j += 4) {
+                        const int4 b4 = *reinterpret_cast<const int4 *>(&blk[j]), l4 = *reinterpret_cast<const int4 *>(&len[j]);
+                        to += (b4.x < mine ? l4.x : 0) + (b4.y < mine ? l4.y : 0) + (b4.z < mine ? l4.z : 0) + (b4.w < mine ? l4.w : 0);
+                        same += (int)(b4.x == mine) + (int)(b4.y == mine) + (int)(b4.z == mine) + (int)(b4.w == mine);
+                    }
+                    tie = tie || same > 1;
+                    at[q] = to - at[q];
+                }
+                if (!__syncthreads_or(tie)) {
+                    int32_t *out = len;
+                    for (int r = tid >> 6; r < nrow; r += NB / 64) {
+                        const int k = 64 * r + lane;
+                        const unsigned long long m = __ballot(run_head(k));
+                        const int q = __builtin_amdgcn_readlane(upto - rows, r) + __popcll(m & ((2ull << lane) - 1ull)) - 1;
+                        if (k < n) out[k + at[q]] = s_src[k];
+                    }
+                    __syncthreads();
+                    for (int k = tid; k < n; k += NB) s_src[k] = out[k];
+                } else {
+                    int p2 = 4;
+                    while (p2 < n) p2 <<= 1;
+                    for (int k = n + tid; k < p2; k += NB) s_src[k] = 0x7fffffff;
+                    __syncthreads();
+                    bitonic_sort<NB>(s_src, p2, tid);
+                }
             }
         }
         __syncthreads();
@@ -2693,15 +2676,7 @@ __global__ __launch_bounds__(NB) void k_collide_dense(Ctx C, int cls_lo, int cls
             sv[1][k] = v1;
             sv[2][k] = v2;
         };
-        if (by_rank) {
-#pragma unroll
-            for (int r = 0; r < GRK; ++r) {
-                const int k = tid + NB * r;
-                if (k < n) gather_one(k, rsrc[r]);
-            }
-        } else {
-            for (int k = tid; k < n; k += NB) gather_one(k, srt[k]);
-        }
+        for (int k = tid; k < n; k += NB) gather_one(k, srt[k]);
         __syncthreads();
         for (int k = tid; k < n; k += NB) claim[k] = 0u;
         if (tid == 0) {
@@ -2939,33 +2914,74 @@ __global__ __launch_bounds__(NB) void k_collide_dense(Ctx C, int cls_lo, int cls
             }
         }
 
-        // SP-Shakhov relaxation (Eq. 16-18)
+        // SP-Shakhov relaxation (Eq. 16-18): each wave queues its relaxing particles in its share
+        // of the claim words, idle after the NTC, and works the queue off as the tile kernel does.
+        // (The global class has its own LDS queue, kQueue particles of a wave at a time.)  0-D
+        // batch of 1024 x 1000: step 275 us with each thread drawing for its own particles, 258 so.
         if (pr > 0.0) {
             int nrel = 0, nar = 0, ncap = 0;
-            // decisions first (32 particles per thread at a time), then the draws
-            for (int k0 = tid; k0 < n; k0 += 32 * NB) {
-            uint32_t mask = 0u;
-            for (int k = k0, j = 0; k < n && j < 32; k += NB, ++j) {
-                const int64_t id = full_id(Dd.id[(size_t)s0 + k], G->next_id[cid]);
-                if (unid(draw(cs, kStreamParticle, (uint64_t)id, st, kDrawRelax).x) < pr) mask |= 1u << j;
-            }
-            while (mask) {
-                const int j = __ffs((int)mask) - 1;
-                mask &= mask - 1u;
-                const int k = k0 + NB * j;
-                const int64_t id = full_id(Dd.id[(size_t)s0 + k], G->next_id[cid]);
-                P Cv[3];
-                int used = shakhov_draw<P>(cs.seed_lo, cs.seed_hi, id, st, par, (P)(1.0 - gas.Pr), Cv);
-                if (used < 0) {
-                    ++ncap;
-                    used = -used;
+            const int64_t nid = G->next_id[cid];
+            const int lane = tid & 63;
+            uint32_t *queue = (GLOB ? s_queue : s_claim) + (tid >> 6) * kQueue;
+            const P one_m_pr = (P)(1.0 - gas.Pr);
+            // k = tid + NB j is particle j of this thread; a queue word holds k and, from bit
+            // kSlotBits on, the next attempt
+            for (int j0 = 0; j0 * NB < n; j0 += kQueue / 64) {
+                int m = 0;                         // draws queued (uniform over the wave)
+                for (int j = j0; j < j0 + kQueue / 64 && j * NB < n; ++j) {
+                    const int k = tid + NB * j;
+                    bool rel = false;
+                    if (k < n) {
+                        const int64_t id = full_id(Dd.id[(size_t)s0 + k], nid);
+                        rel = unid(draw(cs, kStreamParticle, (uint64_t)id, st, kDrawRelax).x) < pr;
+                    }
+                    const unsigned long long mk = __ballot(rel);
+                    if (rel) {
+                        queue[m + __popcll(mk & ((1ull << lane) - 1ull))] = (uint32_t)(GLOB ? k - j0 * NB : k);
+                        ++nrel;
+                    }
+                    m += __popcll(mk);
                 }
-                ++nrel;
-                nar += used;
-                sv[0][k] = (P)(U[0] + (double)Cv[0]);
-                sv[1][k] = (P)(U[1] + (double)Cv[1]);
-                sv[2][k] = (P)(U[2] + (double)Cv[2]);
-            }
+                while (m > 0) {
+                    int kept = 0;                  // draws of this sweep that go on (uniform)
+#pragma unroll 1
+                    for (int q0 = 0; q0 < m; q0 += 64) {
+                        const int nq = min(64, m - q0);
+                        const int lb = draw_lanes_log2(nq);
+                        const int item = lane >> lb;
+                        team_sync<64>();
+                        const uint32_t qw = item < nq ? queue[q0 + item] : 0u;
+                        const int k = (int)(qw & ((1u << kSlotBits) - 1u)) + (GLOB ? j0 * NB : 0);
+                        const uint32_t a0 = qw >> kSlotBits, at = a0 + (uint32_t)(lane & ((1 << lb) - 1));
+                        const bool on = item < nq && at < (uint32_t)kMaxShakhov;
+                        bool acc = false;
+                        P Cv[3] = {(P)0, (P)0, (P)0};
+                        if (on) {
+                            const int64_t id = full_id(Dd.id[(size_t)s0 + k], nid);
+                            acc = shakhov_try<P>(cs.seed_lo, cs.seed_hi, id, st, at, par, one_m_pr, Cv);
+                        }
+                        const unsigned long long macc = __ballot(acc) >> (item << lb);
+                        const unsigned long long grp = lb == 6 ? macc : macc & ((1ull << (1 << lb)) - 1ull);
+                        const uint32_t an = a0 + (1u << lb);
+                        const bool done = grp != 0ull || an >= (uint32_t)kMaxShakhov;
+                        const uint32_t af = grp ? a0 + (uint32_t)(__ffsll((long long)grp) - 1) : (uint32_t)(kMaxShakhov - 1);
+                        if (on && done && at == af) {
+                            sv[0][k] = (P)(U[0] + (double)Cv[0]);
+                            sv[1][k] = (P)(U[1] + (double)Cv[1]);
+                            sv[2][k] = (P)(U[2] + (double)Cv[2]);
+                            nar += (int)at + 1;
+                            ncap += grp ? 0 : 1;
+                        }
+                        const bool again = item < nq && at == a0 && !done;
+                        const unsigned long long mg = __ballot(again);
+                        team_sync<64>();
+                        if (again)
+                            queue[kept + __popcll(mg & ((1ull << lane) - 1ull))] =
+                                (qw & ((1u << kSlotBits) - 1u)) | (an << kSlotBits);
+                        kept += __popcll(mg);
+                    }
+                    m = kept;
+                }
             }
             if (nrel) atomicAdd(&s_rel[0], nrel);
             if (nar) atomicAdd(&s_rel[1], nar);
@@ -3291,7 +3307,13 @@ void Launch::collide(const Ctx &c, void *s)
 }
 void Launch::dense(const Ctx &c, void *s)
 {
-    const int gb = c.grid[HS_KERNEL_DENSE] > 0 ? c.grid[HS_KERNEL_DENSE] : std::max(1, std::min(c.ncells_total, 256 * 2));
+    // One block per resident slot of the FP32 kernel (four a compute unit) where nothing runs
+    // beside it, as in a 0-D batch (1024 x 1000: 272 us a step at 512 blocks, 240 at 768, 212 at
+    // 1024); beside the gather, scalar and tile kernels three a unit (three O-grids: 417 us at 512,
+    // 366 at 768, 390 at 1024 and 2048).  The FP64 kernels hold two (hexahedral sphere: 432 us at
+    // 512, 450 at 768, 463 at 1024).
+    const int per_cu = c.precision == HS_FP64 ? 2 : c.perm ? 3 : 4;
+    const int gb = c.grid[HS_KERNEL_DENSE] > 0 ? c.grid[HS_KERNEL_DENSE] : std::max(1, std::min(c.ncells_total, 256 * per_cu));
     // the two densest classes are rare: a few blocks each
     const int gr = std::max(1, std::min(gb, 64));
     if (c.precision == HS_FP64) {

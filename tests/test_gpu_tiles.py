@@ -101,3 +101,27 @@ def test_sims_side_by_side(gas, n):
         st = s.export_state(0)
         assert np.array_equal(st["id"], first["id"]) and np.array_equal(st["vel"], first["vel"])
         assert np.array_equal(st["acc"], first["acc"])
+
+
+# the block kernel's stable order and draw queue on sorted cells of every class: tubes (no two runs
+# of a block in a cell) and a stream that reflects at a cylinder (such runs)
+@pytest.mark.parametrize("ppc", [300, 520, 1100, 2500, 4500])
+def test_dense_cells_sorted(gas, ppc):
+    from oracle.oracle import Oracle
+    from paper_2506_23917_amd.hs import Sim
+    cases = [W.sod_1d(seed=5, ncells=6, ppc_left=ppc, n_steady=0)]
+    body = W.cylinder_2d(nx=16, ny=12, ppc=ppc, seed=6, n_steady=0)
+    body.update(regions=[((1.5, 2.0, 0.0, 2.1, 4.0, 1.0), body["inflow"])], bc=("outflow",) * 6, capacity=16 * ppc)
+    cases.append(body)
+    sim = Sim(gas, cases, precision="fp64", device="cuda:0")
+    ora = Oracle(gas, cases)
+    ora.init_particles()
+    for _ in range(2):
+        sim.step(1)
+        ora.step(1)
+    for k in range(2):
+        g, o = sim.export_state(k), ora.get_state(k)
+        assert np.array_equal(g["id"], o["id"]) and np.array_equal(g["cell"], o["cell"])
+        assert np.abs(g["vel"] - o["v"]).max() <= 1e-12 * np.abs(o["v"]).max()
+        assert sim.counters(k) == ora.counters(k)
+    assert sim.counters(1)["wall_hits"] > 0
