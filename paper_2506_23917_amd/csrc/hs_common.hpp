@@ -100,7 +100,6 @@ struct Globals {
     int32_t n_work;          // particles routed to the body-reflection kernel
     int32_t n_tiles;         // tiles of the collide kernel this step
     int32_t pad;
-    int32_t case_tile0[kMaxCases + 1];   // first tile of each case (tiles never span cases)
     int64_t next_id[kMaxCases];
     int64_t inj_id_base[kMaxCases];
     int64_t n_samples[kMaxCases];
@@ -184,7 +183,7 @@ struct Launch {
     static void init_fill(const Ctx &c, void *stream);
     static void init_finish(const Ctx &c, void *stream);
     static void scan_cells(const Ctx &c, void *stream, int build_big);
-    static void tile_table(const Ctx &c, void *stream);
+    static void tile_table(const Ctx &c, void *stream, int build_big);
     static void inject(const Ctx &c, void *stream);
     static void move_count(const Ctx &c, void *stream, int any_body);
     static void scatter(const Ctx &c, void *stream);

@@ -465,12 +465,18 @@ __device__ __forceinline__ void add_dense(const Ctx &C, int g, int n, bool dense
 }
 
 // ------------------------------------------------------------------------------------
-// Exclusive scan of per-cell counts (three phases: block sums, scan of block sums,
-// block-local scan + offset).  Each block covers kScanTile cells.
+// Exclusive scan of the per-cell counts.  A block covers kScanTile cells and finds what lies
+// before them itself: from the block sums of k_scan_reduce, or, in batches of up to kScanDirect
+// blocks, from the counts.  Every launch costs a small batch about five microseconds (a kernel's
+// first loads all miss, each XCD's L2 starting empty of what others wrote).  Two or three launches
+// instead of five (block sums scanned and cases tiled by one block each, dense cells listed sixteen
+// to a thread): restart box 95 -> 80 us a step, FP64 tube 159 -> 145, three O-grids 359 -> 337,
+// 800 x 600 cylinder 1012 -> 996.
 // ------------------------------------------------------------------------------------
 
 constexpr int kScanItems = 16;
 constexpr int kScanTile = kBlock * kScanItems;
+constexpr int kScanDirect = 8;
 
 __device__ __forceinline__ int block_excl_scan(int v, int *lds, int &total)
 {
@@ -489,37 +495,80 @@ __device__ __forceinline__ int block_excl_scan(int v, int *lds, int &total)
     return before + incl - v;
 }
 
-__global__ void k_scan_reduce(Ctx C)
+// Sum of v over the block, in every thread.
+__device__ __forceinline__ int block_sum(int v, int *lds)
+{
+    int total;
+    block_excl_scan(v, lds, total);
+    __syncthreads();
+    return total;
+}
+
+// The kScanItems counts from cell `base` on (zero past the last cell).
+__device__ __forceinline__ int load_counts(const Ctx &C, int base, int (&v)[kScanItems])
+{
+    int s = 0;
+#pragma unroll
+    for (int q = 0; q < kScanItems; q += 4) {
+        int4 w = {0, 0, 0, 0};
+        if (base + q + 3 < C.ncells_total) {
+            w = *reinterpret_cast<const int4 *>(C.count + base + q);
+        } else {
+            if (base + q < C.ncells_total) w.x = C.count[base + q];
+            if (base + q + 1 < C.ncells_total) w.y = C.count[base + q + 1];
+            if (base + q + 2 < C.ncells_total) w.z = C.count[base + q + 2];
+        }
+        v[q] = w.x;
+        v[q + 1] = w.y;
+        v[q + 2] = w.z;
+        v[q + 3] = w.w;
+        s += w.x + w.y + w.z + w.w;
+    }
+    return s;
+}
+
+__global__ __launch_bounds__(kBlock) void k_scan_reduce(Ctx C)
+{
+    if (C.g->halt) return;
+    __shared__ int lds[16];
+    int v[kScanItems];
+    const int total = block_sum(load_counts(C, blockIdx.x * kScanTile + threadIdx.x * kScanItems, v), lds);
+    if (threadIdx.x == 0) C.scan_part[blockIdx.x] = total;
+}
+
+// (The counts are cleared by k_tile_table: other blocks read them here.)
+__global__ __launch_bounds__(kBlock) void k_scan_final(Ctx C, int direct)
 {
     if (C.g->halt) return;
     __shared__ int lds[16];
     const int base = blockIdx.x * kScanTile + threadIdx.x * kScanItems;
-    int s = 0;
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        const int g = base + k;
-        if (g < C.ncells_total) s += C.count[g];
+    int v[kScanItems];
+    int before = 0;
+    if (direct) {
+        for (int b = 0; b < (int)blockIdx.x; ++b) before += load_counts(C, b * kScanTile + threadIdx.x * kScanItems, v);
+    } else {
+        for (int b = threadIdx.x; b < (int)blockIdx.x; b += kBlock) before += C.scan_part[b];
     }
+    before = blockIdx.x > 0 ? block_sum(before, lds) : 0;
+    const int s = load_counts(C, base, v);
     int total;
-    block_excl_scan(s, lds, total);
-    if (threadIdx.x == 0) C.scan_part[blockIdx.x] = total;
-}
-
-__global__ void k_scan_parts(Ctx C, int nparts)
-{
-    if (C.g->halt) return;
-    __shared__ int lds[16];
-    int carry = 0;
-    for (int base = 0; base < nparts; base += blockDim.x) {
-        const int i = base + threadIdx.x;
-        const int v = i < nparts ? C.scan_part[i] : 0;
-        int total;
-        const int ex = block_excl_scan(v, lds, total);
-        __syncthreads();
-        if (i < nparts) C.scan_part[i] = carry + ex;
-        carry += total;
+    int run = before + block_excl_scan(s, lds, total);
+#pragma unroll
+    for (int q = 0; q < kScanItems; q += 4) {
+        const int4 w = {run, run + v[q], run + v[q] + v[q + 1], run + v[q] + v[q + 1] + v[q + 2]};
+        run = w.w + v[q + 3];
+        if (base + q + 3 < C.ncells_total) {
+            *reinterpret_cast<int4 *>(C.cstart + base + q) = w;
+        } else {
+            if (base + q < C.ncells_total) C.cstart[base + q] = w.x;
+            if (base + q + 1 < C.ncells_total) C.cstart[base + q + 1] = w.y;
+            if (base + q + 2 < C.ncells_total) C.cstart[base + q + 2] = w.z;
+        }
     }
-    if (threadIdx.x == 0) C.scan_part[nparts] = carry;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        C.cstart[C.ncells_total] = before + total;
+        C.g->n_new = before + total;
+    }
 }
 
 // Collide tiles never span two cases, so a case is tiled exactly as it would be alone (its
@@ -527,15 +576,17 @@ __global__ void k_scan_parts(Ctx C, int nparts)
 // of the case whose local weight w(c) = (cstart[c] - cstart[cell0]) + 4 (c - cell0), which
 // strictly increases, lies in [t TW, (t+1) TW); tile_cell[] holds the first cell of every
 // tile of the batch and, after the last, ncells.
-__global__ void k_case_tiles(Ctx C)
+// One thread per cell; each block works out the cases' first tiles for itself.  Also clears the
+// cell's count for the next move and, with `build_big`, lists the cell if it is dense.
+__global__ __launch_bounds__(kBlock) void k_tile_table(Ctx C, int build_big)
 {
     if (C.g->halt) return;
+    static_assert(kMaxCases <= kBlock, "a thread per case");
     __shared__ int lds[16];
-    Globals *G = C.g;
+    __shared__ int s_tile0[kMaxCases + 1];     // first tile of each case
     const long long tw = C.tile_w;
-    int carry = 0;
-    for (int base = 0; base < C.n_cases; base += blockDim.x) {
-        const int k = base + threadIdx.x;
+    {
+        const int k = threadIdx.x;
         int v = 0;
         if (k < C.n_cases) {
             const CaseDev &cs = C.cases[k];
@@ -544,71 +595,42 @@ __global__ void k_case_tiles(Ctx C)
         }
         int total;
         const int ex = block_excl_scan(v, lds, total);
-        __syncthreads();
-        if (k < C.n_cases) G->case_tile0[k] = carry + ex;
-        carry += total;
-    }
-    if (threadIdx.x == 0) {
-        G->case_tile0[C.n_cases] = carry;
-        G->n_tiles = carry;
-        C.tile_cell[carry] = C.ncells_total;
-    }
-}
-
-__global__ void k_tile_table(Ctx C)
-{
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= C.ncells_total || C.g->halt) return;
-    const int k = case_of(C, g);
-    const CaseDev &cs = C.cases[k];
-    const long long tw = C.tile_w;
-    const long long c0 = C.cstart[cs.cell0];
-    const long long w0 = (C.cstart[g] - c0) + 4ll * (g - cs.cell0);
-    const long long w1 = (C.cstart[g + 1] - c0) + 4ll * (g + 1 - cs.cell0);
-    const int t0 = C.g->case_tile0[k], ntk = C.g->case_tile0[k + 1] - t0;
-    int32_t *tc = C.tile_cell + t0;
-    int32_t *tk = C.tile_case + t0;
-    for (long long t = w0 / tw + 1; t <= w1 / tw; ++t) {
-        tc[t] = g + 1;
-        if (t < ntk) tk[t] = k;
-    }
-    if (g == cs.cell0) {
-        tc[0] = g;
-        tk[0] = k;
-    }
-    if (g == cs.cell0 + cs.ncells - 1 && w1 % tw != 0) tc[w1 / tw + 1] = g + 1;
-}
-
-__global__ void k_scan_final(Ctx C, int build_big, int nparts)
-{
-    if (C.g->halt) return;
-    __shared__ int lds[16];
-    const int base = blockIdx.x * kScanTile + threadIdx.x * kScanItems;
-    int v[kScanItems];
-    int s = 0;
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        const int g = base + k;
-        v[k] = g < C.ncells_total ? C.count[g] : 0;
-        s += v[k];
-    }
-    int total;
-    int run = C.scan_part[blockIdx.x] + block_excl_scan(s, lds, total);
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        const int g = base + k;
-        if (g < C.ncells_total) {
-            C.cstart[g] = run;
-            C.count[g] = 0;
+        if (k < C.n_cases) s_tile0[k] = ex;
+        if (k == 0) {
+            s_tile0[C.n_cases] = total;
+            if (blockIdx.x == 0) {
+                C.g->n_tiles = total;
+                C.tile_cell[total] = C.ncells_total;
+            }
         }
-        if (build_big) add_dense(C, g, v[k], g < C.ncells_total && v[k] > C.cap_wave);
-        run += v[k];
+        __syncthreads();
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        const int all = C.scan_part[nparts];
-        C.cstart[C.ncells_total] = all;
-        C.g->n_new = all;
+    const int g = blockIdx.x * blockDim.x + threadIdx.x;
+    const bool in = g < C.ncells_total;
+    int n = 0;
+    if (in) {
+        const int k = case_of(C, g);
+        const CaseDev &cs = C.cases[k];
+        const long long c0 = C.cstart[cs.cell0];
+        const int s0 = C.cstart[g], s1 = C.cstart[g + 1];
+        n = s1 - s0;
+        const long long w0 = (s0 - c0) + 4ll * (g - cs.cell0);
+        const long long w1 = (s1 - c0) + 4ll * (g + 1 - cs.cell0);
+        const int t0 = s_tile0[k], ntk = s_tile0[k + 1] - t0;
+        int32_t *tc = C.tile_cell + t0;
+        int32_t *tk = C.tile_case + t0;
+        for (long long t = w0 / tw + 1; t <= w1 / tw; ++t) {
+            tc[t] = g + 1;
+            if (t < ntk) tk[t] = k;
+        }
+        if (g == cs.cell0) {
+            tc[0] = g;
+            tk[0] = k;
+        }
+        if (g == cs.cell0 + cs.ncells - 1 && w1 % tw != 0) tc[w1 / tw + 1] = g + 1;
+        C.count[g] = 0;
     }
+    if (build_big) add_dense(C, g, n, in && n > C.cap_wave);
 }
 
 // ------------------------------------------------------------------------------------
@@ -3226,19 +3248,17 @@ void Launch::init_finish(const Ctx &c, void *s)
 {
     hipLaunchKernelGGL(k_init_finish, dim3(1), dim3(256), 0, S_(s), c, (int64_t)0);
 }
-void Launch::tile_table(const Ctx &c, void *s)
+void Launch::tile_table(const Ctx &c, void *s, int build_big)
 {
-    hipLaunchKernelGGL(k_case_tiles, dim3(1), dim3(kBlock), 0, S_(s), c);
-    hipLaunchKernelGGL(k_tile_table, dim3((c.ncells_total + kBlock - 1) / kBlock), dim3(kBlock), 0, S_(s), c);
+    hipLaunchKernelGGL(k_tile_table, dim3(blocks_for(c.ncells_total, kBlock)), dim3(kBlock), 0, S_(s), c, build_big);
 }
 
 void Launch::scan_cells(const Ctx &c, void *s, int build_big)
 {
-    const int nparts = blocks_for(c.ncells_total, kScanTile);
-    hipLaunchKernelGGL(k_scan_reduce, dim3(nparts), dim3(kBlock), 0, S_(s), c);
-    hipLaunchKernelGGL(k_scan_parts, dim3(1), dim3(1024), 0, S_(s), c, nparts);
-    hipLaunchKernelGGL(k_scan_final, dim3(nparts), dim3(kBlock), 0, S_(s), c, build_big, nparts);
-    tile_table(c, s);
+    const int nparts = blocks_for(c.ncells_total, kScanTile), direct = nparts <= kScanDirect ? 1 : 0;
+    if (!direct) hipLaunchKernelGGL(k_scan_reduce, dim3(nparts), dim3(kBlock), 0, S_(s), c);
+    hipLaunchKernelGGL(k_scan_final, dim3(nparts), dim3(kBlock), 0, S_(s), c, direct);
+    tile_table(c, s, build_big);
 }
 void Launch::inject(const Ctx &c, void *s)
 {

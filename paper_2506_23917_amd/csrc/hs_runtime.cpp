@@ -1324,7 +1324,7 @@ hs_status hs_import_state(hs_sim *s, int c, const void *host_buf, size_t bytes)
     G.dt_next[c] = kInfBits;
     G.t_sampled[c] = hd.t_sampled;
     HIPCHK(s, hipMemcpy(at(s, s->lay.globals), &G, sizeof(G), hipMemcpyHostToDevice));
-    Launch::tile_table(s->ctx, s->stream);
+    Launch::tile_table(s->ctx, s->stream, 0);
     HIPCHK(s, hipGetLastError());
     HIPCHK(s, hipStreamSynchronize(s->stream));
     if (!s->plan.any_spatial) {

@@ -125,3 +125,22 @@ def test_dense_cells_sorted(gas, ppc):
         assert np.abs(g["vel"] - o["v"]).max() <= 1e-12 * np.abs(o["v"]).max()
         assert sim.counters(k) == ora.counters(k)
     assert sim.counters(1)["wall_hits"] > 0
+
+
+# cell counts around the scan's block size (4096) and the last one scanned without block sums
+@pytest.mark.parametrize("ncells", [1, 3, 4094, 4096, 4098, 32766, 32768, 32770])
+@pytest.mark.parametrize("ncases", [1, 3])
+def test_scan_sizes(gas, ncells, ncases):
+    from oracle.oracle import Oracle
+    from paper_2506_23917_amd.hs import Sim
+    cases = [W.sod_1d(seed=3 + k, ncells=max(ncells, 1) if k == 0 else 2 + 4 * k, ppc_left=8, n_steady=0)
+             for k in range(ncases)]
+    sim = Sim(gas, cases, precision="fp64", device="cuda:0")
+    ora = Oracle(gas, cases)
+    ora.init_particles()
+    sim.step(2)
+    ora.step(2)
+    for k in range(ncases):
+        g, o = sim.export_state(k), ora.get_state(k)
+        assert np.array_equal(g["id"], o["id"]) and np.array_equal(g["cell"], o["cell"])
+        assert np.array_equal(g["acc"][:, 0], np.asarray(ora.get_cells(k)["acc"])[:, 0])
