@@ -172,6 +172,7 @@ struct Ctx {
     int32_t cap_block, precision, tile_w, dim_max;   // cap_block: densest cell worked on in LDS; dim_max: largest case dimension
     int32_t n_surf_total;         // surface elements of the batch (one copy)
     int64_t capacity;             // total particle capacity of the batch
+    int32_t inject_lanes;         // lanes per inflow face (a power of two, 8 to 64)
     // launch shapes (blocks per grid; 0 = the built-in default), chosen by the autotuner
     int32_t grid[HS_NUM_KERNELS];
 };

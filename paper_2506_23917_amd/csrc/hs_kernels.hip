@@ -637,31 +637,55 @@ __global__ __launch_bounds__(kBlock) void k_tile_table(Ctx C, int build_big)
 // Inflow injection (Step 2 freestream boundaries)
 // ------------------------------------------------------------------------------------
 
+// Particles that enter through inflow face f this step.
+__device__ __forceinline__ int face_count(const Ctx &C, int f, uint32_t st)
+{
+    const FaceDev fd = C.faces[f];
+    const CaseDev &cs = C.cases[fd.case_id];
+    const W4 w = draw(cs, kStreamFace, (uint64_t)fd.local, st, 0);
+    // lambda is per dt_G; an adapted global step (Eq. 26) scales it
+    const double lam = cs.adapt_dt ? fd.lambda * (C.g->dt_cur[fd.case_id] / cs.dt_G) : fd.lambda;
+    return (int)floor(lam + unid(w.x));
+}
+
 __global__ void k_inject_count(Ctx C)
 {
     const int f = blockIdx.x * blockDim.x + threadIdx.x;
     if (f >= C.n_faces || C.g->halt) return;
-    const FaceDev fd = C.faces[f];
-    const CaseDev &cs = C.cases[fd.case_id];
-    const W4 w = draw(cs, kStreamFace, (uint64_t)fd.local, (uint32_t)C.g->step, 0);
-    // lambda is per dt_G; an adapted global step (Eq. 26) scales it
-    const double lam = cs.adapt_dt ? fd.lambda * (C.g->dt_cur[fd.case_id] / cs.dt_G) : fd.lambda;
-    C.face_cnt[f] = (int)floor(lam + unid(w.x));
+    C.face_cnt[f] = face_count(C, f, (uint32_t)C.g->step);
 }
 
-__global__ void k_inject_scan(Ctx C)
+// First new particle of every face: one block, four faces a thread and pass (one a thread took 37
+// us on the 28,672 faces of the 96 x 64 x 64 sphere, four 21).  With `direct`, batches of up
+// to kInjectDirect faces (one pass), the faces are counted here too, one launch less.
+constexpr int kInjectDirect = 4096;
+
+__global__ __launch_bounds__(1024) void k_inject_scan(Ctx C, int direct)
 {
     if (C.g->halt) return;
     __shared__ int lds[16];
     Globals *G = C.g;
+    const uint32_t st = (uint32_t)G->step;
     int carry = 0;
-    for (int base = 0; base < C.n_faces; base += blockDim.x) {
-        const int i = base + threadIdx.x;
-        const int v = i < C.n_faces ? C.face_cnt[i] : 0;
+    for (int base = 0; base < C.n_faces; base += 4 * (int)blockDim.x) {
+        const int f = base + 4 * (int)threadIdx.x;
+        int v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[k] = 0;
+            if (f + k < C.n_faces) v[k] = direct ? face_count(C, f + k, st) : C.face_cnt[f + k];
+        }
         int total;
-        const int ex = block_excl_scan(v, lds, total);
+        int run = carry + block_excl_scan(v[0] + v[1] + v[2] + v[3], lds, total);
         __syncthreads();
-        if (i < C.n_faces) C.face_start[i] = carry + ex;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (f + k < C.n_faces) {
+                C.face_start[f + k] = run;
+                if (direct) C.face_cnt[f + k] = v[k];
+            }
+            run += v[k];
+        }
         carry += total;
     }
     if (threadIdx.x == 0) C.face_start[C.n_faces] = carry;
@@ -682,14 +706,18 @@ __global__ void k_inject_scan(Ctx C)
     }
 }
 
-// One wavefront per inflow face; lanes stride over the face's new particles.  The launch
-// bound lets the hexahedral placement keep its nodes in registers (without it the compiler
-// assumes 1024-thread blocks, caps the kernel at 128 VGPRs and spills about 700).
-template <typename P>
+// inject_lanes lanes per inflow face stride over its new particles: the power of two that holds
+// what the busiest face expects (whole waves left 60 of 64 lanes idle on the faces of the 96 x 64 x
+// 64 sphere: its step 928 -> 898 us with this and the scan above).  MESH: 0 without a mesh case in the batch; the mesh placements take 256 registers
+// and scratch, the grid's alone about 110.  The launch bound lets the hexahedral
+// placement keep its nodes in registers (without it the compiler assumes 1024-thread blocks, caps
+// the kernel at 128 VGPRs and spills about 700).
+template <typename P, int MESH>
 __global__ __launch_bounds__(kBlock) void k_inject_fill(Ctx C)
 {
-    const int f = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
+    const int nl = C.inject_lanes;
+    const int f = (int)(blockIdx.x * blockDim.x + threadIdx.x) / nl;
+    const int lane = threadIdx.x & (nl - 1);
     if (f >= C.n_faces || C.g->halt) return;
     const int cnt = C.face_cnt[f];
     if (cnt == 0) return;
@@ -706,7 +734,7 @@ __global__ __launch_bounds__(kBlock) void k_inject_fill(Ctx C)
     const int64_t slot0 = (int64_t)C.g->n_live + C.face_start[f];
     const int64_t id0 = C.g->inj_id_base[fd.case_id] + (C.face_start[f] - C.face_start[cs.face0]);
     long long capped = 0;
-    if (cs.mesh && cs.dim == 3) {
+    if (MESH && cs.mesh && cs.dim == 3) {
         // a hexahedron's face: inward normal n = -nf / |nf|; tangents t1, t2 by Gram-Schmidt
         // from the two axes other than the one n is most aligned with; points from the face's
         // bilinear map (origin: the corner of smallest t1 + t2 coordinate, u towards its
@@ -758,7 +786,7 @@ __global__ __launch_bounds__(kBlock) void k_inject_fill(Ctx C)
             }
         const double snm = dot3(cs.in_u, n) * beta;
         const double ut1 = dot3(cs.in_u, t1), ut2 = dot3(cs.in_u, t2);
-        for (int q = lane; q < cnt; q += 64) {
+        for (int q = lane; q < cnt; q += nl) {
             const uint32_t base = (uint32_t)(1 + 128 * q);
             double u = 0.5, vv = 0.5;
             for (int r = 0; r < 32; ++r) {
@@ -785,7 +813,7 @@ __global__ __launch_bounds__(kBlock) void k_inject_fill(Ctx C)
             S.cell[i] = fd.cell;
             S.id[i] = (uint32_t)(id0 + q);
         }
-    } else if (cs.mesh) {
+    } else if (MESH && cs.mesh) {
         // a mesh edge: inward normal n = (-e_y, e_x) / |e|, in-plane tangent t = (-n_y, n_x)
         // or its opposite (t_x + t_y >= 0), points along +t from the end of smaller t.x
         double Pq[4][2];
@@ -800,7 +828,7 @@ __global__ __launch_bounds__(kBlock) void k_inject_fill(Ctx C)
         if (Bn[0] * tx + Bn[1] * ty < A[0] * tx + A[1] * ty) { S0 = Bn; E0 = A; }
         const double snm = (cs.in_u[0] * nx + cs.in_u[1] * ny) * beta;
         const double ut = cs.in_u[0] * tx + cs.in_u[1] * ty;
-        for (int q = lane; q < cnt; q += 64) {
+        for (int q = lane; q < cnt; q += nl) {
             const uint32_t base = (uint32_t)(1 + 128 * q);
             const W4 wp = draw(cs, kStreamFace, (uint64_t)fd.local, st, base);
             const double frac = unid(wp.x);
@@ -824,7 +852,7 @@ __global__ __launch_bounds__(kBlock) void k_inject_fill(Ctx C)
             S.id[i] = (uint32_t)(id0 + q);
         }
     } else
-    for (int q = lane; q < cnt; q += 64) {
+    for (int q = lane; q < cnt; q += nl) {
         const uint32_t base = (uint32_t)(1 + 128 * q);
         double xr[3] = {0.0, 0.0, 0.0}, v[3];
         const W4 wp = draw(cs, kStreamFace, (uint64_t)fd.local, st, base);
@@ -3263,12 +3291,18 @@ void Launch::scan_cells(const Ctx &c, void *s, int build_big)
 void Launch::inject(const Ctx &c, void *s)
 {
     if (c.n_faces == 0) return;
-    hipLaunchKernelGGL(k_inject_count, dim3(blocks_for(c.n_faces, kBlock)), dim3(kBlock), 0, S_(s), c);
-    hipLaunchKernelGGL(k_inject_scan, dim3(1), dim3(1024), 0, S_(s), c);
-    if (c.precision == HS_FP64)
-        hipLaunchKernelGGL(k_inject_fill<double>, dim3(blocks_for(c.n_faces, 4)), dim3(kBlock), 0, S_(s), c);
-    else
-        hipLaunchKernelGGL(k_inject_fill<float>, dim3(blocks_for(c.n_faces, 4)), dim3(kBlock), 0, S_(s), c);
+    const int direct = c.n_faces <= kInjectDirect ? 1 : 0;
+    if (!direct) hipLaunchKernelGGL(k_inject_count, dim3(blocks_for(c.n_faces, kBlock)), dim3(kBlock), 0, S_(s), c);
+    hipLaunchKernelGGL(k_inject_scan, dim3(1), dim3(1024), 0, S_(s), c, direct);
+    const dim3 grid(blocks_for(c.n_faces, kBlock / c.inject_lanes)), block(kBlock);
+    const bool mesh = c.mxy || c.hxyz;
+    if (c.precision == HS_FP64) {
+        if (mesh) hipLaunchKernelGGL((k_inject_fill<double, 1>), grid, block, 0, S_(s), c);
+        else hipLaunchKernelGGL((k_inject_fill<double, 0>), grid, block, 0, S_(s), c);
+    } else {
+        if (mesh) hipLaunchKernelGGL((k_inject_fill<float, 1>), grid, block, 0, S_(s), c);
+        else hipLaunchKernelGGL((k_inject_fill<float, 0>), grid, block, 0, S_(s), c);
+    }
 }
 void Launch::move_count(const Ctx &c, void *s, int any_body)
 {

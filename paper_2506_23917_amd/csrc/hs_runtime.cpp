@@ -898,6 +898,10 @@ hs_status create_sim(const hs_gas *gas, const hs_case *cases, int n_cases, hs_pr
     c.cap_block = cap_block(prec);
     c.precision = prec;
     c.capacity = s->plan.capacity;
+    double busiest = 0.0;
+    for (const FaceDev &f : s->plan.faces) busiest = std::max(busiest, f.lambda);
+    c.inject_lanes = 8;
+    while (c.inject_lanes < 64 && c.inject_lanes < busiest) c.inject_lanes *= 2;
 
     auto up = [&](size_t off, const void *src, size_t bytes) -> hipError_t {
         if (!bytes) return hipSuccess;

@@ -144,3 +144,24 @@ def test_scan_sizes(gas, ncells, ncases):
         g, o = sim.export_state(k), ora.get_state(k)
         assert np.array_equal(g["id"], o["id"]) and np.array_equal(g["cell"], o["cell"])
         assert np.array_equal(g["acc"][:, 0], np.asarray(ora.get_cells(k)["acc"])[:, 0])
+
+
+# inflow faces counted in the scan or apart, and lanes per face from 8 to 64 (a few to hundreds of
+# new particles a face and step)
+@pytest.mark.parametrize("ny,ppc", [(6, 4), (6, 60), (12, 900), (4095, 2), (4096, 2), (4097, 2), (9000, 2)])
+def test_injection_sizes(gas, ny, ppc):
+    from oracle.oracle import Oracle
+    from paper_2506_23917_amd.hs import Sim
+    st = dict(n=W.N_INF, u=(W.U_INF, 0.0, 0.0), T=W.T_INF)
+    case = W.cylinder_2d(nx=16, ny=12, ppc=8)
+    case.update(nx=2, ny=ny, h=(0.1, 0.1, 1.0), bc=("inflow",) + ("outflow",) * 5, body="none", n_surf=0, regions=[],
+                F_N=W.N_INF * 0.01 / ppc, dt_G=0.09 / W.U_INF, inflow=st, capacity=3 * ny * ppc + 64)
+    sim = Sim(gas, case, precision="fp64", device="cuda:0")
+    ora = Oracle(gas, case)
+    ora.init_particles()
+    sim.step(2)
+    ora.step(2)
+    g, o = sim.export_state(0), ora.get_state(0)
+    assert len(g["id"]) > ny * ppc // 2 and np.array_equal(g["id"], o["id"]) and np.array_equal(g["cell"], o["cell"])
+    assert np.abs(g["vel"] - o["v"]).max() <= 1e-12 * np.abs(o["v"]).max()
+    assert sim.counters(0) == ora.counters(0)
