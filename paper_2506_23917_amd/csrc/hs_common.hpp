@@ -14,6 +14,9 @@ namespace hsk {
 constexpr int kMaxCases = 256;
 constexpr unsigned long long kInfBits = 0x7FF0000000000000ull;   // +inf as double bits
 constexpr int kSurfCopies = 16;     // copies of the wall sums, so few atomics share an address
+constexpr int kCntCopies = 8;       // copies of the event counters, one per XCD
+constexpr int kCntLine = 16;        // words of a copy: a cache line of its own
+constexpr int kCntCase = kCntCopies * kCntLine;
 constexpr int kMaxBounce = 8;        // body reflections per particle per step
 constexpr int kMaxCross = 4096;      // mesh edge crossings per particle per step
 constexpr int kMaxShakhov = 64;      // Shakhov acceptance-rejection attempts
@@ -103,12 +106,16 @@ struct Globals {
     int64_t next_id[kMaxCases];
     int64_t inj_id_base[kMaxCases];
     int64_t n_samples[kMaxCases];
-    long long counters[kMaxCases][HS_NUM_COUNTERS];
     double dt_cur[kMaxCases];                // global step of the current step
     unsigned long long dt_next[kMaxCases];   // Eq. 26 minimum so far (bits of a positive double)
     double t_sampled[kMaxCases];             // sum of the global steps of the sampled steps
     int32_t n_big[kDenseClasses];            // cells of each size class of the block-per-cell kernel
+    // the host reads this record at each synchronising call, and copies of up to 16 KB take the
+    // runtime's slower way (16 us, above that 10)
+    char tail[8192];
 };
+
+static_assert(sizeof(Globals) > 16384, "copied by the copy engine");
 
 // Cell trace record (same field order as hs_trace).
 struct TraceDev {
@@ -167,6 +174,7 @@ struct Ctx {
     // its 8 global node ids and 8 neighbour words (faces 0-5, then 2 unused)
     const double *hxyz;
     const int32_t *hnode, *hnbr;
+    long long *counters;          // n_cases x kCntCopies x kCntLine event counters
     Globals *g;
     int32_t n_cases, n_faces, ncells_total, cap_wave;   // cap_wave: densest cell of the tile kernel
     int32_t cap_block, precision, tile_w, dim_max;   // cap_block: densest cell worked on in LDS; dim_max: largest case dimension

@@ -166,6 +166,15 @@ __device__ __forceinline__ void team_sum(double (&v)[K], double *red)
     }
 }
 
+// The first case's event counters in this block's copy (the others kCntCase words on): a copy per
+// XCD (block b runs on XCD b mod 8), so a counter's cache line stays in one XCD's L2.  With one copy
+// the lines went from XCD to XCD under the adds of thousands of blocks a launch: step of the 96 x
+// 64 x 64 sphere 901 us, 833 so; jets 237 and 217, FP64 hexahedral sphere 377 and 365.
+__device__ __forceinline__ long long *my_counters(const Ctx &C)
+{
+    return C.counters + (blockIdx.x % kCntCopies) * kCntLine;
+}
+
 // Add `val` to base[key] for every active lane, one atomic per distinct key in the wave.
 __device__ __forceinline__ void wave_add(long long *base, int stride, int key, int idx, long long val, bool active)
 {
@@ -425,7 +434,7 @@ __global__ void k_init_finish(Ctx C, int64_t step0)
         G->dt_cur[c] = cs.dt_G;
         G->dt_next[c] = kInfBits;
         G->t_sampled[c] = 0.0;
-        for (int k = 0; k < HS_NUM_COUNTERS; ++k) G->counters[c][k] = 0;
+        for (int k = 0; k < kCntCase; ++k) C.counters[(size_t)c * kCntCase + k] = 0;
         if (np > cs.capacity) raise_error(G, kErrCapacity);
     }
     if (t == 0) {
@@ -697,7 +706,7 @@ __global__ __launch_bounds__(1024) void k_inject_scan(Ctx C, int direct)
         if (live + inj > cs.capacity) raise_error(G, kErrCapacity);
         G->inj_id_base[c] = G->next_id[c];
         G->next_id[c] += inj;
-        G->counters[c][HS_CNT_INJECTED] += inj;
+        my_counters(C)[(size_t)c * kCntCase + HS_CNT_INJECTED] += inj;
     }
     if (threadIdx.x == 0) {
         G->n_inject = carry;
@@ -879,7 +888,7 @@ __global__ __launch_bounds__(kBlock) void k_inject_fill(Ctx C)
         S.cell[i] = fd.cell;
         S.id[i] = (uint32_t)(id0 + q);
     }
-    if (capped) atomicAdd((unsigned long long *)&C.g->counters[fd.case_id][HS_CNT_INJECT_CAP], (unsigned long long)capped);
+    if (capped) atomicAdd((unsigned long long *)&my_counters(C)[(size_t)fd.case_id * kCntCase + HS_CNT_INJECT_CAP], (unsigned long long)capped);
 }
 
 // Counter sums of one wave by case.  Lane l holds counter base + (l & 7) of slot l >> 3
@@ -897,7 +906,7 @@ __device__ __forceinline__ void tally_flush(const Ctx &C, CaseTally &T, int base
 {
     const int k = threadIdx.x & 7;
     if (T.slot_case >= 0 && k < K && T.val != 0)
-        atomicAdd((unsigned long long *)&C.g->counters[T.slot_case][base + k], (unsigned long long)T.val);
+        atomicAdd((unsigned long long *)&my_counters(C)[(size_t)T.slot_case * kCntCase + base + k], (unsigned long long)T.val);
     T.val = 0;
     T.slot_case = -1;
     T.nslot = 0;
@@ -1047,7 +1056,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) 
                 mine = C.cases[cid].mesh == 0;
                 if (mine) move_fast_one<P>(C.cases[cid], S, i, g, xr, v, st, n_live, G->dt_cur[cid], &G->next_id[cid], nc, to_body);
             }
-            wave_add(&G->counters[0][0], HS_NUM_COUNTERS, cid, HS_CNT_REMOVED, 1, mine && !to_body && nc < 0);
+            wave_add(my_counters(C), kCntCase, cid, HS_CNT_REMOVED, 1, mine && !to_body && nc < 0);
         }
         // worklist of body candidates
         {
@@ -1125,9 +1134,9 @@ __global__ __launch_bounds__(kBlock) void k_move_mesh(Ctx C)
         }
         const int myslot = wave_slot(C.count, nc, mine && nc >= 0);
         if (mine && nc >= 0) C.slot[i] = myslot;
-        wave_add(&G->counters[0][0], HS_NUM_COUNTERS, cid, HS_CNT_REMOVED, 1, mine && nc < 0);
-        wave_add(&G->counters[0][0], HS_NUM_COUNTERS, cid, HS_CNT_WALL_HITS, ms.hits, mine);
-        wave_add(&G->counters[0][0], HS_NUM_COUNTERS, cid, HS_CNT_BOUNCE_CAP, ms.capped, mine);
+        wave_add(my_counters(C), kCntCase, cid, HS_CNT_REMOVED, 1, mine && nc < 0);
+        wave_add(my_counters(C), kCntCase, cid, HS_CNT_WALL_HITS, ms.hits, mine);
+        wave_add(my_counters(C), kCntCase, cid, HS_CNT_BOUNCE_CAP, ms.capped, mine);
     }
 }
 
@@ -1178,9 +1187,9 @@ __global__ __launch_bounds__(kBlock) void k_move_body(Ctx C)
         }
         const int myslot = wave_slot(C.count, nc, valid && nc >= 0);
         if (valid && nc >= 0) C.slot[i] = myslot;
-        wave_add(&G->counters[0][0], HS_NUM_COUNTERS, cid, HS_CNT_REMOVED, 1, valid && nc < 0);
-        wave_add(&G->counters[0][0], HS_NUM_COUNTERS, cid, HS_CNT_WALL_HITS, ms.hits, valid);
-        wave_add(&G->counters[0][0], HS_NUM_COUNTERS, cid, HS_CNT_BOUNCE_CAP, ms.capped, valid);
+        wave_add(my_counters(C), kCntCase, cid, HS_CNT_REMOVED, 1, valid && nc < 0);
+        wave_add(my_counters(C), kCntCase, cid, HS_CNT_WALL_HITS, ms.hits, valid);
+        wave_add(my_counters(C), kCntCase, cid, HS_CNT_BOUNCE_CAP, ms.capped, valid);
     }
 }
 
@@ -1236,28 +1245,13 @@ __device__ __forceinline__ int draw_lanes_log2(int n)
 
 __device__ __forceinline__ void flush_counts(const Ctx &C, int cid, CellCounts &cc)
 {
-    long long *cnt = &C.g->counters[cid][0];
+    long long *cnt = my_counters(C) + (size_t)cid * kCntCase;
     if (cc.cand) atomicAdd((unsigned long long *)&cnt[HS_CNT_CANDIDATES], (unsigned long long)cc.cand);
     if (cc.acc) atomicAdd((unsigned long long *)&cnt[HS_CNT_ACCEPTED], (unsigned long long)cc.acc);
     if (cc.relax) atomicAdd((unsigned long long *)&cnt[HS_CNT_RELAXED], (unsigned long long)cc.relax);
     if (cc.ar) atomicAdd((unsigned long long *)&cnt[HS_CNT_AR_ATTEMPTS], (unsigned long long)cc.ar);
     if (cc.arcap) atomicAdd((unsigned long long *)&cnt[HS_CNT_AR_CAP], (unsigned long long)cc.arcap);
     if (cc.skipped) atomicAdd((unsigned long long *)&cnt[HS_CNT_SKIPPED_CELLS], (unsigned long long)cc.skipped);
-    cc = CellCounts{0, 0, 0, 0, 0, 0};
-}
-
-// Kernel-end flush of every lane's counts: one atomic per counter and distinct case in the
-// wave (same-address atomics from every lane of every block would serialise in L2).
-__device__ __forceinline__ void wave_flush_counts(const Ctx &C, int cid, CellCounts &cc)
-{
-    long long *base = &C.g->counters[0][0];
-    const bool on = cid >= 0;
-    wave_add(base, HS_NUM_COUNTERS, cid, HS_CNT_CANDIDATES, cc.cand, on);
-    wave_add(base, HS_NUM_COUNTERS, cid, HS_CNT_ACCEPTED, cc.acc, on);
-    wave_add(base, HS_NUM_COUNTERS, cid, HS_CNT_RELAXED, cc.relax, on);
-    wave_add(base, HS_NUM_COUNTERS, cid, HS_CNT_AR_ATTEMPTS, cc.ar, on);
-    wave_add(base, HS_NUM_COUNTERS, cid, HS_CNT_AR_CAP, cc.arcap, on);
-    wave_add(base, HS_NUM_COUNTERS, cid, HS_CNT_SKIPPED_CELLS, cc.skipped, on);
     cc = CellCounts{0, 0, 0, 0, 0, 0};
 }
 

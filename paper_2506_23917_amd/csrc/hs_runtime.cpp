@@ -28,7 +28,7 @@ constexpr uint32_t kMagic = 0x48534331u;  // "HSC1"
 struct Layout {
     size_t total = 0;
     size_t scratch_begin = 0;
-    size_t globals, cases, faces, rbox, rstate, dtcell;
+    size_t globals, counters, cases, faces, rbox, rstate, dtcell;
     size_t pos[2][3], vel[2][3], cell[2], id[2];
     size_t newcell, slot, perm, work, count, cstart, sigc, acc, vol, facecnt, facestart, scanpart, big, tiles, tilecase, cellrec, surf, trace, out;
     size_t mxy = 0, mquad = 0, mnbr = 0, mgeo = 0, hxyz = 0, hnode = 0, hnbr = 0;
@@ -550,6 +550,7 @@ Layout make_layout(const Plan &P, hs_precision prec, uint32_t flags)
     const size_t nc = (size_t)P.ncells;
     // ---- the sim's data
     L.globals = take(sizeof(Globals));
+    L.counters = take(sizeof(long long) * kCntCase * P.cases.size());
     L.cases = take(sizeof(CaseDev) * P.cases.size());
     L.faces = take(sizeof(FaceDev) * std::max<size_t>(P.faces.size(), 1));
     L.rbox = take(sizeof(double) * std::max<size_t>(P.rbox.size(), 1));
@@ -667,12 +668,9 @@ hs_status read_globals(hs_sim *s, Globals &G)
     return HS_OK;
 }
 
-hs_status check_device(hs_sim *s)
+// Reports the errors latched in the globals G.
+hs_status latched(hs_sim *s, const Globals &G)
 {
-    if (s->failed) return HS_ERR_STATE;
-    Globals G;
-    hs_status st = read_globals(s, G);
-    if (st) return st;
     if (G.err) {
         std::string why = "device error:";
         hs_status code = HS_ERR_STATE;
@@ -684,6 +682,15 @@ hs_status check_device(hs_sim *s)
         return code;
     }
     return HS_OK;
+}
+
+hs_status check_device(hs_sim *s)
+{
+    if (s->failed) return HS_ERR_STATE;
+    Globals G;
+    hs_status st = read_globals(s, G);
+    if (st) return st;
+    return latched(s, G);
 }
 
 void enqueue_step(hs_sim *s, int timed)
@@ -891,6 +898,7 @@ hs_status create_sim(const hs_gas *gas, const hs_case *cases, int n_cases, hs_pr
     c.dim_max = s->plan.dim_max;
     c.trace = (flags & HS_FLAG_TRACE) ? (TraceDev *)at(s, L.trace) : nullptr;
     c.g = (Globals *)at(s, L.globals);
+    c.counters = (long long *)at(s, L.counters);
     c.n_cases = n_cases;
     c.n_faces = (int32_t)s->plan.faces.size();
     c.ncells_total = (int32_t)s->plan.ncells;
@@ -1352,11 +1360,24 @@ hs_status hs_last_trace(hs_sim *s, int c, hs_trace *out)
 hs_status hs_counters(hs_sim *s, int c, int64_t *out)
 {
     if (!s || !out || c < 0 || c >= (int)s->plan.cases.size()) return HS_ERR_ARG;
-    hs_status st = check_device(s);
-    if (st) return st;
+    if (s->failed) return HS_ERR_STATE;
+    // one copy for the globals and the counters that follow them, up to the case's
+    constexpr size_t words = sizeof(long long) * kCntCase;
+    const size_t first = s->lay.counters - s->lay.globals + words * (size_t)c;
+    std::vector<char> buf(first + words);
+    HIPCHK(s, hipStreamSynchronize(s->stream));
+    HIPCHK(s, hipMemcpy(buf.data(), at(s, s->lay.globals), buf.size(), hipMemcpyDeviceToHost));
     Globals G;
-    if ((st = read_globals(s, G))) return st;
-    for (int k = 0; k < HS_NUM_COUNTERS; ++k) out[k] = G.counters[c][k];
+    std::memcpy(&G, buf.data(), sizeof(G));
+    const hs_status st = latched(s, G);
+    if (st) return st;
+    // the case's lines of all copies, added up
+    long long v[kCntCopies][kCntLine];
+    std::memcpy(v, buf.data() + first, sizeof(v));
+    for (int k = 0; k < HS_NUM_COUNTERS; ++k) {
+        out[k] = 0;
+        for (int j = 0; j < kCntCopies; ++j) out[k] += v[j][k];
+    }
     return HS_OK;
 }
 
