@@ -1280,6 +1280,9 @@ __device__ __forceinline__ int chunk_shift(int ntiles)
 // send their own: that kernel runs two waves per SIMD and is bound by instruction issue, its
 // per-lane adds overlap with its arithmetic, and the address-order walk measured slower there.
 constexpr int kSampSpread = 16;
+// Free lanes of the tile kernel before its NTC takes new candidates (preparing them costs the wave
+// the same for one lane as for all; FP32 sphere 808 us a step at 8, 782 at 16, 757 at 32, 771 at 48).
+constexpr int kNtcRefill = 32;
 
 // Eq. 26: fold a wave's smallest local step of case cid (lanes hold their own minima, +inf
 // where none) into the case's minimum for the next global step; one atomic per wave.
@@ -1911,13 +1914,12 @@ __device__ __forceinline__ void collide_tile_body(const Ctx &C)
 {
     constexpr int MAXC = TW / 4;
     constexpr int MAXP = TW + D;
-    constexpr int MAXK = 128;             // NTC candidates per chunk (two per lane)
     static_assert(MAXC <= 64, "one lane per cell at least");
-    // claim word per particle slot: (round << 8) | (255 - candidate), rounds numbered across
+    // claim word per particle slot: (round << 16) | (0xFFFF - candidate), rounds numbered across
     // the whole launch, so words of earlier rounds always lose an atomicMax of this round.
     // Between the NTC of one tile and the next the words hold the queue of Shakhov draws (slot,
-    // cell << 9, next attempt << 15: below 2^21); rounds start above 2^13, so these lose too.
-    constexpr uint32_t kRound0 = 1u << 13;
+    // cell << 9, next attempt << 15: below 2^21); rounds start above 2^5, so these lose too.
+    constexpr uint32_t kRound0 = 1u << 5;
     static_assert(MAXP <= 512 && MAXC <= 64 && kMaxShakhov <= 64, "queue word fits 21 bits");
     __shared__ uint32_t s_claim[MAXP];
     __shared__ P s_v[3][MAXP];
@@ -2157,80 +2159,80 @@ __device__ __forceinline__ void collide_tile_body(const Ctx &C)
         if (lane == 0) c_kb[ncl] = kall;
         team_sync<64>();
 
-        // ---- NTC (Eq. 5-9).  The candidates of a chunk are prepared by all lanes (two per
-        // lane, kept in registers).  Then, in rounds, every pending candidate that is the
-        // lowest-numbered pending user of both its particles is processed: such candidates
-        // share no particle with each other or with an earlier pending candidate, so the
-        // outcome equals the sequential order of Eq. 5-9.  (sigma c)_max is fixed during the
-        // step.
+        // ---- NTC (Eq. 5-9).  Each lane holds one candidate, prepared when the lane takes it (in
+        // candidate order; lanes that are done take new ones, several at a time).  In rounds, every
+        // held candidate that is the lowest-numbered holder of both its particles is processed:
+        // such candidates share no particle with each other or with an earlier one still to do, so
+        // the outcome equals the sequential order of Eq. 5-9.  (sigma c)_max is fixed during the
+        // step.  Two candidates a lane, all done before the next 128 were prepared, took two to
+        // three times the rounds (few lanes had one ready in the last ones) at twice the code each:
+        // FP64 0-D batch of 1999 x 150 188 -> 148 us a step, 332 x 249 cylinder 375 -> 323, FP32
+        // sphere 829 -> 759.
         const P K_vhs = (P)gas.K_vhs, ex_vhs = (P)gas.vhs_exp;
-        for (int kbase = 0; kbase < kall; kbase += MAXK) {
-            const int kn = min(MAXK, kall - kbase);
-            int ci[2], cj[2], clc[2], ck[2];
-            P cu[2], om[2][3];
-            bool pend[2];
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const int q = lane + 64 * r;
-                pend[r] = q < kn;
-                ci[r] = cj[r] = clc[r] = ck[r] = 0;
-                cu[r] = om[r][0] = om[r][1] = om[r][2] = (P)0;
-                if (pend[r]) {
-                    const int x = kbase + q;
-                    int a = 0, b = ncl - 1;
-                    while (a < b) {
-                        const int mid = (a + b + 1) >> 1;
-                        if (c_kb[mid] <= x) a = mid;
-                        else b = mid - 1;
-                    }
-                    const int kc = x - c_kb[a];
-                    const int o2 = c_off[a], cn = c_off[a + 1] - o2;
-                    const uint32_t lcid = (uint32_t)(lc0 + a);
-                    const W4 w = draw_s(sd0, sd1, kStreamCell, lcid, st, (uint32_t)(1 + 2 * kc));
-                    const uint32_t i = unidx(w.x, (uint32_t)cn);
-                    uint32_t j = unidx(w.y, (uint32_t)(cn - 1));
-                    if (j >= i) ++j;
-                    ci[r] = o2 + (int)i;
-                    cj[r] = o2 + (int)j;
-                    clc[r] = a;
-                    ck[r] = kc;
-                    cu[r] = Real<P>::uni(w.z);
-                    const W4 w2 = draw_s(sd0, sd1, kStreamCell, lcid, st, (uint32_t)(2 + 2 * kc));
-                    const P cchi = (P)2 * Real<P>::uni(w2.x) - (P)1;
-                    const P schi = Real<P>::sq((P)1 - cchi * cchi);
-                    P sth, cth;
-                    Real<P>::sc2pi(Real<P>::uni(w2.y), &sth, &cth);
-                    om[r][0] = cchi;
-                    om[r][1] = schi * cth;
-                    om[r][2] = schi * sth;
-                }
-            }
+        {
+            int ci = 0, cj = 0, clc = 0, ck = 0;
+            P cu = (P)0, om[3] = {(P)0, (P)0, (P)0};
+            bool pend = false;
+            int x = 0;                         // candidate held by this lane (of the tile's kall)
+            int next = 0, base = 0;            // first one not taken yet, number 0 of the claims
             for (;;) {
-                if (!__any(pend[0] || pend[1])) break;
-                if (round == 0xffffffu) {          // round counter exhausted: clear the claims
+                const unsigned long long freem = __ballot(!pend);
+                const int nfree = __popcll(freem);
+                if (next < kall && (nfree >= kNtcRefill || nfree == 64)) {
+                    // claim numbers count from the lowest held candidate (it is always processed, so the
+                    // held ones span at most 64 rounds of 64)
+                    if (next - base > 0xF000) base = nfree == 64 ? next : -wave_max(pend ? -x : -next);
+                    const int mine = next + __popcll(freem & ((1ull << lane) - 1ull));
+                    if (!pend && mine < kall) {
+                        x = mine;
+                        pend = true;
+                        int a = 0, b = ncl - 1;
+                        while (a < b) {
+                            const int mid = (a + b + 1) >> 1;
+                            if (c_kb[mid] <= x) a = mid;
+                            else b = mid - 1;
+                        }
+                        const int kc = x - c_kb[a];
+                        const int o2 = c_off[a], cn = c_off[a + 1] - o2;
+                        const uint32_t lcid = (uint32_t)(lc0 + a);
+                        const W4 w = draw_s(sd0, sd1, kStreamCell, lcid, st, (uint32_t)(1 + 2 * kc));
+                        const uint32_t i = unidx(w.x, (uint32_t)cn);
+                        uint32_t j = unidx(w.y, (uint32_t)(cn - 1));
+                        if (j >= i) ++j;
+                        ci = o2 + (int)i;
+                        cj = o2 + (int)j;
+                        clc = a;
+                        ck = kc;
+                        cu = Real<P>::uni(w.z);
+                        const W4 w2 = draw_s(sd0, sd1, kStreamCell, lcid, st, (uint32_t)(2 + 2 * kc));
+                        const P cchi = (P)2 * Real<P>::uni(w2.x) - (P)1;
+                        const P schi = Real<P>::sq((P)1 - cchi * cchi);
+                        P sth, cth;
+                        Real<P>::sc2pi(Real<P>::uni(w2.y), &sth, &cth);
+                        om[0] = cchi;
+                        om[1] = schi * cth;
+                        om[2] = schi * sth;
+                    }
+                    next = min(kall, next + nfree);
+                } else if (nfree == 64) {
+                    break;
+                }
+                if (round == 0xffffu) {            // round counter exhausted: clear the claims
                     team_sync<64>();
                     for (int s2 = lane; s2 < MAXP; s2 += 64) s_claim[s2] = 0u;
                     round = kRound0;
                     team_sync<64>();
                 }
                 ++round;
-                uint32_t tag[2];
-#pragma unroll
-                for (int r = 0; r < 2; ++r) {
-                    tag[r] = (round << 8) | (uint32_t)(255 - (lane + 64 * r));
-                    if (pend[r]) {
-                        atomicMax(&s_claim[ci[r]], tag[r]);
-                        atomicMax(&s_claim[cj[r]], tag[r]);
-                    }
+                const uint32_t tag = (round << 16) | (uint32_t)(0xFFFF - (x - base));
+                if (pend) {
+                    atomicMax(&s_claim[ci], tag);
+                    atomicMax(&s_claim[cj], tag);
                 }
                 team_sync<64>();
-#pragma unroll
-                for (int r = 0; r < 2; ++r) {
-                    if (!pend[r]) continue;
-                    const int i = ci[r], j = cj[r];
-                    if (s_claim[i] != tag[r] || s_claim[j] != tag[r]) continue;
-                    pend[r] = false;
-                    const int lc = clc[r];
+                if (pend && s_claim[ci] == tag && s_claim[cj] == tag) {
+                    pend = false;
+                    const int i = ci, j = cj, lc = clc;
                     P *vx = s_v[0], *vy = s_v[1], *vz = s_v[2];
                     const P gx = vx[i] - vx[j], gy = vy[i] - vy[j], gz = vz[i] - vz[j];
                     const P cr = Real<P>::sq(gx * gx + gy * gy + gz * gz);
@@ -2243,16 +2245,16 @@ __device__ __forceinline__ void collide_tile_body(const Ctx &C)
                         atomicMax(&c_obs[lc], (unsigned long long)__double_as_longlong(sc));
                     else
                         atomicMax(&c_obs[lc], __float_as_uint(sc));
-                    if (cu[r] < sc / c_scm[lc]) {
+                    if (cu < sc / c_scm[lc]) {
                         const P sx = vx[i] + vx[j], sy = vy[i] + vy[j], sz = vz[i] + vz[j];
-                        vx[i] = (P)0.5 * (sx - cr * om[r][0]);
-                        vx[j] = (P)0.5 * (sx + cr * om[r][0]);
-                        vy[i] = (P)0.5 * (sy - cr * om[r][1]);
-                        vy[j] = (P)0.5 * (sy + cr * om[r][1]);
-                        vz[i] = (P)0.5 * (sz - cr * om[r][2]);
-                        vz[j] = (P)0.5 * (sz + cr * om[r][2]);
+                        vx[i] = (P)0.5 * (sx - cr * om[0]);
+                        vx[j] = (P)0.5 * (sx + cr * om[0]);
+                        vy[i] = (P)0.5 * (sy - cr * om[1]);
+                        vy[j] = (P)0.5 * (sy + cr * om[1]);
+                        vz[i] = (P)0.5 * (sz - cr * om[2]);
+                        vz[j] = (P)0.5 * (sz + cr * om[2]);
                         atomicAdd(&c_nacc[lc], 1);
-                        atomicXor(&c_hash[lc], (UWord)((unsigned long long)(ck[r] + 1) * 0x9E3779B97F4A7C15ull));
+                        atomicXor(&c_hash[lc], (UWord)((unsigned long long)(ck + 1) * 0x9E3779B97F4A7C15ull));
                     }
                 }
                 team_sync<64>();
@@ -3345,13 +3347,14 @@ void Launch::scalars(const Ctx &c, void *s)
 }
 void Launch::collide(const Ctx &c, void *s)
 {
-    // FP64 tiles differ most in length (its acceptance-rejection draws): 8192 blocks, a tile or
-    // two each, keep the chip even (332 x 249 cylinder, us a step: 745 at 1024 blocks, 600 at
-    // 4096, 550 at 8192 and 16384); FP32 at 4096 (800 x 600 cylinder: 1069; 8192 1091)
+    // tiles differ in length (their NTC rounds and acceptance-rejection draws): 8192 blocks, a few
+    // tiles each, keep the chip even (FP64 332 x 249 cylinder, us a step: 745 at 1024 blocks, 600
+    // at 4096, 550 at 8192 and 16384; FP32 sphere 759 at 4096, 741 at 8192, 800 x 600 cylinder 977
+    // and 969)
     if (c.precision == HS_FP64)
         hipLaunchKernelGGL(k_collide_tile_f64, dim3(tile_grid(c, HS_KERNEL_COLLIDE, 256ll * 32)), dim3(64), 0, S_(s), c);
     else
-        hipLaunchKernelGGL(k_collide_tile_f32, dim3(tile_grid(c, HS_KERNEL_COLLIDE, 256ll * 16)), dim3(64), 0, S_(s), c);
+        hipLaunchKernelGGL(k_collide_tile_f32, dim3(tile_grid(c, HS_KERNEL_COLLIDE, 256ll * 32)), dim3(64), 0, S_(s), c);
 }
 void Launch::dense(const Ctx &c, void *s)
 {

@@ -165,3 +165,30 @@ def test_injection_sizes(gas, ny, ppc):
     assert len(g["id"]) > ny * ppc // 2 and np.array_equal(g["id"], o["id"]) and np.array_equal(g["cell"], o["cell"])
     assert np.abs(g["vel"] - o["v"]).max() <= 1e-12 * np.abs(o["v"]).max()
     assert sim.counters(0) == ora.counters(0)
+
+
+# the NTC's candidate window: fewer candidates than lanes, about as many, and thousands on a few
+# particles (long chains of candidates sharing a particle), alone and in tiles of several cells
+@pytest.mark.parametrize("ncells,ppc,rate", [(1, 2, 1.0), (1, 2, 2000.0), (1, 60, 0.5), (1, 192, 1.0), (5, 40, 30.0),
+                                             (30, 4, 300.0), (2, 100, 100.0)])
+def test_ntc_window(gas, ncells, ppc, rate):
+    from oracle.oracle import Oracle
+    from paper_2506_23917_amd.hs import Sim
+    case = W.relax_0d(ncells=ncells, ppc=ppc)
+    case["dt_over_tau"] = np.full(ncells, 0.9)           # all DSMC
+    v, cell, ids = W.relax_0d_state(case, ppc=ppc)
+    ora = Oracle(gas, case, trace=True)
+    ora.set_state(0, None, v, cell, ids, len(ids), 0)
+    sigc = ora.get_cells(0)["sigc_max"] * rate           # more candidates, each less often accepted
+    ora.set_cells(0, sigc_max=sigc)
+    sim = Sim(gas, case, precision="fp64", trace=True, no_particles=True, device="cuda:0")
+    sim.import_state(0, dict(pos=np.zeros((len(ids), 3)), vel=v, cell=cell, id=ids, next_id=len(ids), step=0,
+                             sigc_max=sigc))
+    for _ in range(2):
+        sim.step(1)
+        ora.step(1)
+        tg, to = sim.trace(0), ora.trace(0)
+        for f in ("n", "ncol", "nacc", "acc_hash"):
+            assert np.array_equal(tg[f], to[f]), f
+    g, o = sim.export_state(0), ora.get_state(0)
+    assert np.abs(g["vel"] - o["v"]).max() <= 1e-12 * np.abs(o["v"]).max()
