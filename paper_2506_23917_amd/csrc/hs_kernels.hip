@@ -2569,14 +2569,12 @@ __device__ __forceinline__ void bitonic_sort(int32_t *a, int p2, int tid)
 template <typename P, int CAPB, int NB, bool GLOB = false>
 __global__ __launch_bounds__(NB) __attribute__((amdgpu_waves_per_eu(sizeof(P) == 4 && CAPB <= kCapBlockMax ? 4 : 1, 8))) void k_collide_dense(Ctx C, int cls_lo, int cls_hi)
 {
-    constexpr int KC = 2 * NB;             // NTC candidates per chunk (two per thread)
-    static_assert(KC <= 1024, "candidate number fits the claim word");
     constexpr int CAPL = GLOB ? 4 : CAPB;  // LDS rows (the global class keeps its cell in memory)
     __shared__ __attribute__((aligned(16))) int32_t s_src[CAPL];   // sources during the gather, then claim words
     __shared__ __attribute__((aligned(16))) P s_v[3][CAPL];
     __shared__ double s_red[(NB / 64) * 12];
     __shared__ unsigned long long s_obs, s_hash;
-    __shared__ int s_nacc, s_left;
+    __shared__ int s_nacc, s_left, s_next;     // accepted; candidates to do and not taken yet
     __shared__ int32_t s_rel[3];
     __shared__ int s_rows[64];                 // runs starting in each row of 64 slots (ranking)
     uint32_t *s_claim = (uint32_t *)s_src;
@@ -2856,71 +2854,68 @@ __global__ __launch_bounds__(NB) __attribute__((amdgpu_waves_per_eu(sizeof(P) ==
         }
         __syncthreads();
 
-        // NTC (Eq. 5-9) in rounds over the block, as in k_collide_tile
+        // NTC (Eq. 5-9) in rounds over the block, a candidate a thread, as in the tile kernel: a
+        // wave with half its lanes free takes the next numbers (the claims go by the candidates'
+        // numbers, so it does not matter which thread holds which).  Numbers of a claim word
+        // reach 2^16: more candidates go in turns of that many.  (0-D batch of 1024 x 1000, 2400
+        // candidates a cell: 215 us a step with chunks of two a thread worked off completely, 172 so.)
         const uint32_t lc = (uint32_t)(g - cs.cell0);
         const P scm = (P)scmax;
         uint32_t round = 0;
-        for (long long kbase = 0; kbase < ncol; kbase += KC) {
-            const int kn = (int)min((long long)KC, ncol - kbase);
-            int ci[2], cj[2];
-            long long ck[2];
-            P cu[2], om[2][3];
-            bool pend[2];
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const int q = tid + NB * r;
-                pend[r] = q < kn;
-                ci[r] = cj[r] = 0;
-                ck[r] = 0;
-                cu[r] = om[r][0] = om[r][1] = om[r][2] = (P)0;
-                if (pend[r]) {
-                    const long long kc = kbase + q;
-                    const W4 w = draw(cs, kStreamCell, lc, st, (uint32_t)(1 + 2 * kc));
-                    const uint32_t i = unidx(w.x, (uint32_t)n);
-                    uint32_t j = unidx(w.y, (uint32_t)(n - 1));
-                    if (j >= i) ++j;
-                    ci[r] = (int)i;
-                    cj[r] = (int)j;
-                    ck[r] = kc;
-                    cu[r] = Real<P>::uni(w.z);
-                    const W4 w2 = draw(cs, kStreamCell, lc, st, (uint32_t)(2 + 2 * kc));
-                    const P cchi = (P)2 * Real<P>::uni(w2.x) - (P)1;
-                    const P schi = Real<P>::sq((P)1 - cchi * cchi);
-                    P sth, cth;
-                    Real<P>::sc2pi(Real<P>::uni(w2.y), &sth, &cth);
-                    om[r][0] = cchi;
-                    om[r][1] = schi * cth;
-                    om[r][2] = schi * sth;
-                }
+        for (long long kbase = 0; kbase < ncol; kbase += 0x10000) {
+            const int kn = (int)min((long long)0x10000, ncol - kbase);
+            int ci = 0, cj = 0, x = -1;            // x: candidate held, from kbase on (-1: none)
+            P cu = (P)0, om[3] = {(P)0, (P)0, (P)0};
+            __syncthreads();                       // every thread has left the previous turn's rounds
+            if (tid == 0) {
+                s_left = kn;
+                s_next = 0;
             }
-            __syncthreads();                   // every thread has left the previous chunk's rounds
-            if (tid == 0) s_left = kn;
             __syncthreads();
             for (;;) {
-                if (round == 0x3fffffu) {      // round counter exhausted: clear the claims
+                const unsigned long long freem = __ballot(x < 0);
+                const int nfree = __popcll(freem);
+                if (nfree >= kNtcRefill) {
+                    const int lane = tid & 63;
+                    int first = 0;
+                    if (lane == 0) first = s_next < kn ? atomicAdd(&s_next, nfree) : kn;
+                    const int mine = __builtin_amdgcn_readfirstlane(first) + __popcll(freem & ((1ull << lane) - 1ull));
+                    if (x < 0 && mine < kn) {
+                        x = mine;
+                        const long long kc = kbase + x;
+                        const W4 w = draw(cs, kStreamCell, lc, st, (uint32_t)(1 + 2 * kc));
+                        const uint32_t i = unidx(w.x, (uint32_t)n);
+                        uint32_t j = unidx(w.y, (uint32_t)(n - 1));
+                        if (j >= i) ++j;
+                        ci = (int)i;
+                        cj = (int)j;
+                        cu = Real<P>::uni(w.z);
+                        const W4 w2 = draw(cs, kStreamCell, lc, st, (uint32_t)(2 + 2 * kc));
+                        const P cchi = (P)2 * Real<P>::uni(w2.x) - (P)1;
+                        const P schi = Real<P>::sq((P)1 - cchi * cchi);
+                        P sth, cth;
+                        Real<P>::sc2pi(Real<P>::uni(w2.y), &sth, &cth);
+                        om[0] = cchi;
+                        om[1] = schi * cth;
+                        om[2] = schi * sth;
+                    }
+                }
+                if (round == 0xffffu) {            // round counter exhausted: clear the claims
                     for (int k = tid; k < n; k += NB) claim[k] = 0u;
                     round = 0;
                     __syncthreads();
                 }
                 ++round;
-                uint32_t tag[2];
-#pragma unroll
-                for (int r = 0; r < 2; ++r) {
-                    tag[r] = (round << 10) | (uint32_t)(1023 - (tid + NB * r));
-                    if (pend[r]) {
-                        atomicMax(&claim[ci[r]], tag[r]);
-                        atomicMax(&claim[cj[r]], tag[r]);
-                    }
+                const uint32_t tag = (round << 16) | (uint32_t)(0xFFFF - x);
+                if (x >= 0) {
+                    atomicMax(&claim[ci], tag);
+                    atomicMax(&claim[cj], tag);
                 }
                 __syncthreads();
-                int done = 0;
-#pragma unroll
-                for (int r = 0; r < 2; ++r) {
-                    if (!pend[r]) continue;
-                    const int i = ci[r], j = cj[r];
-                    if (claim[i] != tag[r] || claim[j] != tag[r]) continue;
-                    pend[r] = false;
-                    ++done;
+                bool done = false;
+                if (x >= 0 && claim[ci] == tag && claim[cj] == tag) {
+                    done = true;
+                    const int i = ci, j = cj;
                     P *vx = sv[0], *vy = sv[1], *vz = sv[2];
                     const P gx = vx[i] - vx[j], gy = vy[i] - vy[j], gz = vz[i] - vz[j];
                     const P cr = Real<P>::sq(gx * gx + gy * gy + gz * gz);
@@ -2931,19 +2926,21 @@ __global__ __launch_bounds__(NB) __attribute__((amdgpu_waves_per_eu(sizeof(P) ==
                     else
                         sc = gas.K_vhs * pow(cr, gas.vhs_exp);
                     atomicMax(&s_obs, (unsigned long long)__double_as_longlong((double)sc));
-                    if (cu[r] < sc / scm) {
+                    if (cu < sc / scm) {
                         const P sx = vx[i] + vx[j], sy = vy[i] + vy[j], sz = vz[i] + vz[j];
-                        vx[i] = (P)0.5 * (sx - cr * om[r][0]);
-                        vx[j] = (P)0.5 * (sx + cr * om[r][0]);
-                        vy[i] = (P)0.5 * (sy - cr * om[r][1]);
-                        vy[j] = (P)0.5 * (sy + cr * om[r][1]);
-                        vz[i] = (P)0.5 * (sz - cr * om[r][2]);
-                        vz[j] = (P)0.5 * (sz + cr * om[r][2]);
+                        vx[i] = (P)0.5 * (sx - cr * om[0]);
+                        vx[j] = (P)0.5 * (sx + cr * om[0]);
+                        vy[i] = (P)0.5 * (sy - cr * om[1]);
+                        vy[j] = (P)0.5 * (sy + cr * om[1]);
+                        vz[i] = (P)0.5 * (sz - cr * om[2]);
+                        vz[j] = (P)0.5 * (sz + cr * om[2]);
                         atomicAdd(&s_nacc, 1);
-                        atomicXor(&s_hash, (unsigned long long)(ck[r] + 1) * 0x9E3779B97F4A7C15ull);
+                        atomicXor(&s_hash, (unsigned long long)(kbase + x + 1) * 0x9E3779B97F4A7C15ull);
                     }
+                    x = -1;
                 }
-                if (done) atomicSub(&s_left, done);
+                const unsigned long long dm = __ballot(done);
+                if (dm && (tid & 63) == 0) atomicSub(&s_left, __popcll(dm));
                 __syncthreads();
                 if (s_left == 0) break;
             }

@@ -192,3 +192,29 @@ def test_ntc_window(gas, ncells, ppc, rate):
             assert np.array_equal(tg[f], to[f]), f
     g, o = sim.export_state(0), ora.get_state(0)
     assert np.abs(g["vel"] - o["v"]).max() <= 1e-12 * np.abs(o["v"]).max()
+
+
+# the block kernel's candidate window: few candidates, thousands, and more than one claim word counts
+@pytest.mark.parametrize("ppc,rate", [(200, 0.01), (200, 30.0), (700, 20.0), (5000, 3.0), (460, 700.0)])
+def test_ntc_window_dense(gas, ppc, rate):
+    from oracle.oracle import Oracle
+    from paper_2506_23917_amd.hs import Sim
+    case = W.relax_0d(ncells=2, ppc=ppc)
+    case["dt_over_tau"] = np.array([0.9, 0.3])           # all DSMC
+    v, cell, ids = W.relax_0d_state(case, ppc=ppc)
+    ora = Oracle(gas, case, trace=True)
+    ora.set_state(0, None, v, cell, ids, len(ids), 0)
+    sigc = ora.get_cells(0)["sigc_max"] * rate
+    ora.set_cells(0, sigc_max=sigc)
+    sim = Sim(gas, case, precision="fp64", trace=True, no_particles=True, device="cuda:0")
+    sim.import_state(0, dict(pos=np.zeros((len(ids), 3)), vel=v, cell=cell, id=ids, next_id=len(ids), step=0,
+                             sigc_max=sigc))
+    sim.step(1)
+    ora.step(1)
+    tg, to = sim.trace(0), ora.trace(0)
+    for f in ("n", "ncol", "nacc", "acc_hash"):
+        assert np.array_equal(tg[f], to[f]), f
+    if rate > 500:
+        assert to["ncol"].max() > 65536
+    g, o = sim.export_state(0), ora.get_state(0)
+    assert np.abs(g["vel"] - o["v"]).max() <= 1e-12 * np.abs(o["v"]).max()
