@@ -3145,7 +3145,12 @@ __global__ void k_finish_step(Ctx C, int sorted)
 // Output (Step 6) and checks
 // ------------------------------------------------------------------------------------
 
-// Current-state Eq. 31 estimators of one case: n, U (3), T, q (3) per cell.
+// Step (6) output of one case: the fields n, U (3 a cell), T and q (3 a cell), one after the
+// other, as the caller's arrays hold them (records of eight doubles a cell went through a host
+// buffer of the same size, faulted in and taken apart at each call: 480,000 cells 5.5 or 11 ms by
+// the state of the host's heap, 2.5 or 7 so).
+
+// Current-state Eq. 31 estimators.
 template <typename P>
 __global__ void k_moments_now(Ctx C, int case_id, double *out)
 {
@@ -3180,18 +3185,16 @@ __global__ void k_moments_now(Ctx C, int case_id, double *out)
             for (int a = 0; a < 3; ++a) q[a] = f * 0.5 * C.gas.m * s3[a];
         }
     }
-    double *o = out + 8 * (size_t)lc;
-    o[0] = vol > 0.0 ? (double)n * cs.F_N / vol : 0.0;
-    o[1] = U[0];
-    o[2] = U[1];
-    o[3] = U[2];
-    o[4] = T;
-    o[5] = q[0];
-    o[6] = q[1];
-    o[7] = q[2];
+    const size_t nc = (size_t)cs.ncells;
+    out[lc] = vol > 0.0 ? (double)n * cs.F_N / vol : 0.0;
+    out[4 * nc + lc] = T;
+    for (int a = 0; a < 3; ++a) {
+        out[nc + 3 * (size_t)lc + a] = U[a];
+        out[5 * nc + 3 * (size_t)lc + a] = q[a];
+    }
 }
 
-// Step (6) time averages of one case from the Step (5) sums: n, U (3), T, q (3) per cell.
+// Time averages from the Step (5) sums.
 __global__ void k_finalize(Ctx C, int case_id, double *out)
 {
     const CaseDev &cs = C.cases[case_id];
@@ -3215,15 +3218,13 @@ __global__ void k_finalize(Ctx C, int case_id, double *out)
             q[a] = 0.5 * C.gas.m * nn * (A[10 + a] / A[0] - 2.0 * uc - U[a] * cc + 2.0 * U[a] * uu);
         }
     }
-    double *o = out + 8 * (size_t)lc;
-    o[0] = nn;
-    o[1] = U[0];
-    o[2] = U[1];
-    o[3] = U[2];
-    o[4] = T;
-    o[5] = q[0];
-    o[6] = q[1];
-    o[7] = q[2];
+    const size_t nc = (size_t)cs.ncells;
+    out[lc] = nn;
+    out[4 * nc + lc] = T;
+    for (int a = 0; a < 3; ++a) {
+        out[nc + 3 * (size_t)lc + a] = U[a];
+        out[5 * nc + 3 * (size_t)lc + a] = q[a];
+    }
 }
 
 __global__ void k_philox(uint64_t seed, uint32_t stream, uint64_t e0, uint32_t step, uint32_t d, int64_t n,

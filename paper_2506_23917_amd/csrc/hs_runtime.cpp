@@ -636,6 +636,12 @@ struct hs_sim {
     };
     std::vector<StepEvents> events;      // one record per timed step
     int64_t timed_steps = 0;
+    // page-locked host memory that fields are read through, in two halves (copy_out); made at the
+    // first read of fields, never by a sim on the static scratch array
+    char *stage = nullptr;
+    size_t stage_half = 0;
+    hipEvent_t ev_stage[2] = {};
+    bool stage_tried = false;
 };
 
 namespace {
@@ -665,6 +671,78 @@ hs_status read_globals(hs_sim *s, Globals &G)
 {
     HIPCHK(s, hipStreamSynchronize(s->stream));
     HIPCHK(s, hipMemcpy(&G, at(s, s->lay.globals), sizeof(Globals), hipMemcpyDeviceToHost));
+    return HS_OK;
+}
+
+constexpr size_t kStageHalf = (size_t)4 << 20;       // most bytes of one half of the staging memory
+
+void make_stage(hs_sim *s)
+{
+    s->stage_tried = true;
+    if (!s->side) return;
+    size_t most = 0;
+    for (const auto &c : s->plan.cases) most = std::max(most, 8 * 8 * (size_t)c.ncells);
+    const size_t half = std::min(kStageHalf, align256(most));
+    void *p = nullptr;
+    hipError_t e = hipHostMalloc(&p, 2 * half, hipHostMallocDefault);
+    for (int k = 0; k < 2 && e == hipSuccess; ++k) e = hipEventCreateWithFlags(&s->ev_stage[k], hipEventDisableTiming);
+    if (e == hipSuccess) {
+        s->stage = (char *)p;
+        s->stage_half = half;
+    } else {
+        if (p) (void)hipHostFree(p);
+        (void)hipGetLastError();           // fields are then copied straight to the caller
+    }
+}
+
+struct CopyPart {
+    void *to;
+    const void *from;                      // device
+    size_t bytes;
+};
+
+// Copies device arrays to pageable host memory after the stream's work, and waits: through
+// page-locked memory, one half filled by the copy engine while the other is emptied (a copy into
+// fresh pageable memory locks and unlocks it page by page).
+hs_status copy_out(hs_sim *s, const CopyPart *part, int n)
+{
+    if (!s->stage_tried) make_stage(s);
+    if (!s->stage) {
+        for (int k = 0; k < n; ++k)
+            if (part[k].bytes) HIPCHK(s, hipMemcpyAsync(part[k].to, part[k].from, part[k].bytes, hipMemcpyDeviceToHost, s->stream));
+        HIPCHK(s, hipStreamSynchronize(s->stream));
+        return HS_OK;
+    }
+    std::vector<CopyPart> held[2];         // pieces on their way through each half
+    auto drain = [&](int h) -> hipError_t {
+        if (held[h].empty()) return hipSuccess;
+        const hipError_t e = hipEventSynchronize(s->ev_stage[h]);
+        if (e != hipSuccess) return e;
+        for (const CopyPart &c : held[h]) std::memcpy(c.to, c.from, c.bytes);
+        held[h].clear();
+        return hipSuccess;
+    };
+    int h = 0;
+    size_t used = 0;
+    for (int k = 0; k < n; ++k) {
+        for (size_t done = 0; done < part[k].bytes;) {
+            const size_t take = std::min(part[k].bytes - done, s->stage_half - used);
+            char *via = s->stage + h * s->stage_half + used;
+            HIPCHK(s, hipMemcpyAsync(via, (const char *)part[k].from + done, take, hipMemcpyDeviceToHost, s->stream));
+            held[h].push_back({(char *)part[k].to + done, via, take});
+            done += take;
+            used += take;
+            if (used == s->stage_half) {
+                HIPCHK(s, hipEventRecord(s->ev_stage[h], s->stream));
+                h ^= 1;
+                used = 0;
+                HIPCHK(s, drain(h));
+            }
+        }
+    }
+    HIPCHK(s, hipEventRecord(s->ev_stage[h], s->stream));
+    HIPCHK(s, drain(h ^ 1));
+    HIPCHK(s, drain(h));
     return HS_OK;
 }
 
@@ -1111,30 +1189,30 @@ hs_status hs_sample_moments(hs_sim *s, int c, int mode, double *n, double *u3, d
                             int64_t *n_samples)
 {
     if (!s || c < 0 || c >= (int)s->plan.cases.size() || (mode != 0 && mode != 1)) return HS_ERR_ARG;
-    hs_status st = check_device(s);
+    if (s->failed) return HS_ERR_STATE;
+    Globals G;
+    hs_status st = read_globals(s, G);
+    if (!st) st = latched(s, G);
     if (st) return st;
-    const int nc = s->plan.cases[c].ncells;
+    const size_t nc = (size_t)s->plan.cases[c].ncells;
     double *out = (double *)at(s, s->lay.out);
-    if (mode == 0) launch_finalize(s->ctx, s->stream, c, nc, out);
-    else launch_moments_now(s->ctx, s->stream, c, nc, out);
-    std::vector<double> h((size_t)nc * 8);
-    HIPCHK(s, hipMemcpyAsync(h.data(), out, h.size() * 8, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipStreamSynchronize(s->stream));
-    for (int k = 0; k < nc; ++k) {
-        const double *o = &h[8 * (size_t)k];
-        if (n) n[k] = o[0];
-        if (T) T[k] = o[4];
-        for (int a = 0; a < 3; ++a) {
-            if (u3) u3[3 * k + a] = o[1 + a];
-            if (q3) q3[3 * k + a] = o[5 + a];
-        }
+    if (mode == 0) launch_finalize(s->ctx, s->stream, c, (int)nc, out);
+    else launch_moments_now(s->ctx, s->stream, c, (int)nc, out);
+    HIPCHK(s, hipGetLastError());
+    // the kernels write the four fields one after the other, each as the caller's array holds it;
+    // arrays that follow each other on the host too are one piece
+    const CopyPart part[4] = {{n, out, n ? 8 * nc : 0},
+                              {u3, out + nc, u3 ? 8 * 3 * nc : 0},
+                              {T, out + 4 * nc, T ? 8 * nc : 0},
+                              {q3, out + 5 * nc, q3 ? 8 * 3 * nc : 0}};
+    if (n && u3 == n + nc && T == n + 4 * nc && q3 == n + 5 * nc) {
+        const CopyPart all{n, out, 8 * 8 * nc};
+        st = copy_out(s, &all, 1);
+    } else {
+        st = copy_out(s, part, 4);
     }
-    if (n_samples) {
-        Globals G;
-        st = read_globals(s, G);
-        if (st) return st;
-        *n_samples = G.n_samples[c];
-    }
+    if (st) return st;
+    if (n_samples) *n_samples = G.n_samples[c];
     return HS_OK;
 }
 
@@ -1538,6 +1616,9 @@ void hs_destroy(hs_sim *s)
     if (s->ev_fork) (void)hipEventDestroy(s->ev_fork);
     if (s->ev_join) (void)hipEventDestroy(s->ev_join);
     if (s->side) (void)hipStreamDestroy(s->side);
+    for (hipEvent_t e : s->ev_stage)
+        if (e) (void)hipEventDestroy(e);
+    if (s->stage) (void)hipHostFree(s->stage);
     delete s;
 }
 
