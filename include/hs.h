@@ -76,8 +76,8 @@ enum {
 enum {
     HS_KERNEL_INJECT = 0,      /* inflow counts, scan and fill (Step 2 freestream faces)     */
     HS_KERNEL_MOVE = 1,        /* free transport, walls, per-cell counts (Step 2)           */
-    HS_KERNEL_SCAN = 2,        /* exclusive scan of the cell counts, tile table             */
-    HS_KERNEL_SCATTER = 3,     /* scatter of particle indices by cell                       */
+    HS_KERNEL_SCAN = 2,        /* exclusive scan of the cell counts                         */
+    HS_KERNEL_SCATTER = 3,     /* scatter of particle indices by cell, tile table           */
     HS_KERNEL_GATHER = 4,      /* stable in-cell order, sorted state written                */
     HS_KERNEL_SCALARS = 5,     /* Step 3 moments, Eq. 10 / 25-28 split, N_col per cell      */
     HS_KERNEL_COLLIDE = 6,     /* Step 4-5 on the tiles: NTC, Shakhov, rescale, sampling    */

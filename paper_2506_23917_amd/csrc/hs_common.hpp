@@ -191,8 +191,8 @@ struct Launch {
     static void init_count(const Ctx &c, void *stream);
     static void init_fill(const Ctx &c, void *stream);
     static void init_finish(const Ctx &c, void *stream);
-    static void scan_cells(const Ctx &c, void *stream, int build_big);
-    static void tile_table(const Ctx &c, void *stream, int build_big);
+    static void scan_cells(const Ctx &c, void *stream);
+    static void tile_table(const Ctx &c, void *stream);
     static void inject(const Ctx &c, void *stream);
     static void move_count(const Ctx &c, void *stream, int any_body);
     static void scatter(const Ctx &c, void *stream);

@@ -587,9 +587,8 @@ __global__ __launch_bounds__(kBlock) void k_scan_final(Ctx C, int direct)
 // tile of the batch and, after the last, ncells.
 // One thread per cell; each block works out the cases' first tiles for itself.  Also clears the
 // cell's count for the next move and, with `build_big`, lists the cell if it is dense.
-__global__ __launch_bounds__(kBlock) void k_tile_table(Ctx C, int build_big)
+__device__ __forceinline__ void tile_table_block(const Ctx &C, int build_big)
 {
-    if (C.g->halt) return;
     static_assert(kMaxCases <= kBlock, "a thread per case");
     __shared__ int lds[16];
     __shared__ int s_tile0[kMaxCases + 1];     // first tile of each case
@@ -640,6 +639,12 @@ __global__ __launch_bounds__(kBlock) void k_tile_table(Ctx C, int build_big)
         C.count[g] = 0;
     }
     if (build_big) add_dense(C, g, n, in && n > C.cap_wave);
+}
+
+__global__ __launch_bounds__(kBlock) void k_tile_table(Ctx C)
+{
+    if (C.g->halt) return;
+    tile_table_block(C, 0);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1193,12 +1198,19 @@ __global__ __launch_bounds__(kBlock) void k_move_body(Ctx C)
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_scatter(Ctx C)
+// Sources to their slots of the sorted order; the first table_blocks blocks build the tile table and
+// list the dense cells meanwhile (both need the scan alone; as a launch of its own the table cost a
+// step 3 to 5 us: FP64 tube 121 and 118, restart box 80 and 76, jets 198 and 193).
+__global__ __launch_bounds__(kBlock) void k_scatter(Ctx C, int table_blocks)
 {
     Globals *G = C.g;
     if (G->halt) return;
-    const int n_total = G->n_total;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_total; i += gridDim.x * blockDim.x) {
+    if ((int)blockIdx.x < table_blocks) {
+        tile_table_block(C, 1);
+        return;
+    }
+    const int n_total = G->n_total, stride = (int)(gridDim.x - table_blocks) * (int)blockDim.x;
+    for (int i = ((int)blockIdx.x - table_blocks) * (int)blockDim.x + (int)threadIdx.x; i < n_total; i += stride) {
         const int nc = C.newcell[i];
         if (nc >= 0) C.perm[C.cstart[nc] + C.slot[i]] = i;
     }
@@ -3270,17 +3282,16 @@ void Launch::init_finish(const Ctx &c, void *s)
 {
     hipLaunchKernelGGL(k_init_finish, dim3(1), dim3(256), 0, S_(s), c, (int64_t)0);
 }
-void Launch::tile_table(const Ctx &c, void *s, int build_big)
+void Launch::tile_table(const Ctx &c, void *s)
 {
-    hipLaunchKernelGGL(k_tile_table, dim3(blocks_for(c.ncells_total, kBlock)), dim3(kBlock), 0, S_(s), c, build_big);
+    hipLaunchKernelGGL(k_tile_table, dim3(blocks_for(c.ncells_total, kBlock)), dim3(kBlock), 0, S_(s), c);
 }
 
-void Launch::scan_cells(const Ctx &c, void *s, int build_big)
+void Launch::scan_cells(const Ctx &c, void *s)
 {
     const int nparts = blocks_for(c.ncells_total, kScanTile), direct = nparts <= kScanDirect ? 1 : 0;
     if (!direct) hipLaunchKernelGGL(k_scan_reduce, dim3(nparts), dim3(kBlock), 0, S_(s), c);
     hipLaunchKernelGGL(k_scan_final, dim3(nparts), dim3(kBlock), 0, S_(s), c, direct);
-    tile_table(c, s, build_big);
 }
 void Launch::inject(const Ctx &c, void *s)
 {
@@ -3318,7 +3329,8 @@ void Launch::scatter(const Ctx &c, void *s)
 {
     const int grid = c.grid[HS_KERNEL_SCATTER] > 0 ? c.grid[HS_KERNEL_SCATTER]
                                                    : std::min(stream_grid(), blocks_for(c.capacity, kBlock));
-    hipLaunchKernelGGL(k_scatter, dim3(grid), dim3(kBlock), 0, S_(s), c);
+    const int table = blocks_for(c.ncells_total, kBlock);
+    hipLaunchKernelGGL(k_scatter, dim3(grid + table), dim3(kBlock), 0, S_(s), c, table);
 }
 // Tile kernels loop over tiles with a fixed grid: wide for the streaming gather and scalar
 // kernels; the collision kernel's per-wave setup and counter flush are paid once per block.

@@ -797,7 +797,7 @@ void enqueue_step(hs_sim *s, int timed)
         Launch::move_count(c, st, s->plan.any_body ? 1 : 0);
         mark(HS_KERNEL_MOVE, false, ms);
         mark(HS_KERNEL_SCAN, true, ms);
-        Launch::scan_cells(c, st, 1);
+        Launch::scan_cells(c, st);
         mark(HS_KERNEL_SCAN, false, ms);
         mark(HS_KERNEL_SCATTER, true, ms);
         Launch::scatter(c, st);
@@ -1022,7 +1022,8 @@ hs_status create_sim(const hs_gas *gas, const hs_case *cases, int n_cases, hs_pr
     Ctx ci = c;
     if (fill) Launch::init_cells(ci, s->stream);
     else Launch::init_count(ci, s->stream);
-    Launch::scan_cells(ci, s->stream, 0);
+    Launch::scan_cells(ci, s->stream);
+    Launch::tile_table(ci, s->stream);
     if (fill) Launch::init_fill(ci, s->stream);
     Launch::init_finish(ci, s->stream);
     if (!s->plan.any_spatial) launch_build_big(ci, s->stream);
@@ -1414,7 +1415,7 @@ hs_status hs_import_state(hs_sim *s, int c, const void *host_buf, size_t bytes)
     G.dt_next[c] = kInfBits;
     G.t_sampled[c] = hd.t_sampled;
     HIPCHK(s, hipMemcpy(at(s, s->lay.globals), &G, sizeof(G), hipMemcpyHostToDevice));
-    Launch::tile_table(s->ctx, s->stream, 0);
+    Launch::tile_table(s->ctx, s->stream);
     HIPCHK(s, hipGetLastError());
     HIPCHK(s, hipStreamSynchronize(s->stream));
     if (!s->plan.any_spatial) {
