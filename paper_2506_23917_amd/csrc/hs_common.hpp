@@ -194,7 +194,7 @@ struct Launch {
     static void scan_cells(const Ctx &c, void *stream);
     static void tile_table(const Ctx &c, void *stream);
     static void inject(const Ctx &c, void *stream);
-    static void move_count(const Ctx &c, void *stream, int any_body);
+    static void move_count(const Ctx &c, void *stream, int any_body, int any_grid);
     static void scatter(const Ctx &c, void *stream);
     static void gather(const Ctx &c, void *stream);
     static void scalars(const Ctx &c, void *stream);

@@ -3309,18 +3309,19 @@ void Launch::inject(const Ctx &c, void *s)
         else hipLaunchKernelGGL((k_inject_fill<float, 0>), grid, block, 0, S_(s), c);
     }
 }
-void Launch::move_count(const Ctx &c, void *s, int any_body)
+void Launch::move_count(const Ctx &c, void *s, int any_body, int any_grid)
 {
     const int grid = c.grid[HS_KERNEL_MOVE] > 0 ? c.grid[HS_KERNEL_MOVE]
                                                 : std::min(4 * stream_grid(), blocks_for(c.capacity, kBlock));
     // the worklist holds the body-near particles of grid cases (about 1%); mesh cases have
-    // their own kernel over the whole particle array
+    // their own kernel over the whole particle array (a batch of meshes alone needs no grid move,
+    // whose pass over its waves took 13 to 15 us)
     if (c.precision == HS_FP64) {
-        hipLaunchKernelGGL(k_move_fast<double>, dim3(grid), dim3(kBlock), 0, S_(s), c);
+        if (any_grid) hipLaunchKernelGGL(k_move_fast<double>, dim3(grid), dim3(kBlock), 0, S_(s), c);
         if (c.mxy || c.hxyz) hipLaunchKernelGGL(k_move_mesh<double>, dim3(grid), dim3(kBlock), 0, S_(s), c);
         if (any_body) hipLaunchKernelGGL(k_move_body<double>, dim3(256), dim3(kBlock), 0, S_(s), c);
     } else {
-        hipLaunchKernelGGL(k_move_fast<float>, dim3(grid), dim3(kBlock), 0, S_(s), c);
+        if (any_grid) hipLaunchKernelGGL(k_move_fast<float>, dim3(grid), dim3(kBlock), 0, S_(s), c);
         if (c.mxy || c.hxyz) hipLaunchKernelGGL(k_move_mesh<float>, dim3(grid), dim3(kBlock), 0, S_(s), c);
         if (any_body) hipLaunchKernelGGL(k_move_body<float>, dim3(256), dim3(kBlock), 0, S_(s), c);
     }

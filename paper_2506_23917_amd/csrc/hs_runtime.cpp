@@ -53,7 +53,7 @@ struct Plan {
     bool any_quad = false, any_hex = false;
     int64_t ncells = 0, capacity = 0;
     int dim_max = 0;
-    bool any_spatial = false, any_0d = false, any_body = false, any_mesh = false;
+    bool any_spatial = false, any_0d = false, any_body = false, any_mesh = false, any_grid = false;   // any_grid: a case without a mesh
     GasDev gas;
 };
 
@@ -536,6 +536,7 @@ void build_plan(const hs_gas *g, const hs_case *cs, int n, Plan &P)
         P.capacity += c.capacity;
         P.dim_max = std::max(P.dim_max, c.dim);
         if (c.dim > 0) P.any_spatial = true;
+        if (!c.mesh) P.any_grid = true;
     }
     P.ncells = cell0;
 }
@@ -794,7 +795,7 @@ void enqueue_step(hs_sim *s, int timed)
         Launch::inject(c, st);
         mark(HS_KERNEL_INJECT, false, ms);
         mark(HS_KERNEL_MOVE, true, ms);
-        Launch::move_count(c, st, s->plan.any_body ? 1 : 0);
+        Launch::move_count(c, st, s->plan.any_body ? 1 : 0, s->plan.any_grid ? 1 : 0);
         mark(HS_KERNEL_MOVE, false, ms);
         mark(HS_KERNEL_SCAN, true, ms);
         Launch::scan_cells(c, st);
