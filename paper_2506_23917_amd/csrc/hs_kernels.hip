@@ -1656,14 +1656,24 @@ __device__ __forceinline__ int group_sum_iv(int x, int kb, int kbmax)
 
 // Steps (3)-(4a) of the tiles' cells: Eq. 31 moments of the sorted velocities, Eq. 10 / 25-28
 // timescales and split, the NTC candidate count and the Shakhov parameters; one record per
-// cell.  Each cell is served by an aligned group of 2^kb lanes (2^kb ncl <= 64): a lane sums
-// every 2^kb-th particle of its cell straight from memory and the group combines the
-// partial sums by a butterfly, so every lane of the group holds the cell's totals and
-// derives the scalars itself; lane `sub == 0` records them.
+// cell.  For the sums each cell of a tile is served by an aligned group of 2^kb lanes (2^kb ncl <=
+// 64): a lane sums every 2^kb-th particle of its cell straight from memory and the group combines
+// the partial sums by a butterfly.  The scalars (a power, an exponential, square roots and a dozen
+// divisions in FP64) cost a wave the same for one cell as for 64, so the sums of the block's next
+// tiles of the same case are collected in LDS, up to 64 cells, and each lane then derives one
+// cell's scalars: kernel on the 800 x 600 cylinder (8 tiles a block, 7 cells a tile) 152 -> 116 us, 227 -> 89 lane-instructions a particle; step
+// 969 -> 939, 96 x 64 x 64 sphere 740 -> 731; batches of a tile or less a block, which have nothing
+// to collect, 1% slower.
 template <typename P, int TW, int D>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_cell_scalars(Ctx C)
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_cell_scalars(Ctx C)
 {
     constexpr int MAXC = TW / 4;
+    constexpr int kBatch = 16;             // most tiles of a batch
+    static_assert(MAXC <= 64, "a tile's cells fit a batch");
+    __shared__ double c_s1[4][64], c_s2[4][64];      // sums of c, |c|^2; peculiar |C|^2, |C|^2 C
+    __shared__ double c_vol[64], c_scm[64];          // volume, (sigma c)_max
+    __shared__ int32_t c_cell[64], c_num[64];        // global cell; particles (-1: dense)
+    __shared__ int32_t b_cb[kBatch], b_m0[kBatch + 1];   // first cell of each tile, its first slot
     Globals *G = C.g;
     if (G->halt) return;
     const int lane = threadIdx.x;
@@ -1685,18 +1695,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8))) void
     int t = xcd_tile(pos, xcd, csh);
     TileRef nx = tile_ref(C, t, ntiles);
     while (t < ntiles) {
-        const TileRef cur = nx;
-        pos += nbx;
-        t = xcd_tile(pos, xcd, csh);
-        nx = tile_ref(C, t, ntiles);
-        const int cb = cur.cb;
-        const int ncl = cur.ce - cb;
-        const int cid = cur.ci;
-        if (ncl < 0 || ncl > MAXC || cb < 0 || cb + ncl > NC || cid < 0 || cid >= C.n_cases) {
+        const int cid = nx.ci;
+        if (cid < 0 || cid >= C.n_cases) {
             if (lane == 0) raise_error(G, kErrState);
             return;
         }
-        if (ncl == 0) continue;
         if (cid != my_case) {
             tally_add<1>(C, tally, my_case, HS_CNT_SKIPPED_CELLS, skipped);
             skipped[0] = 0;
@@ -1705,29 +1708,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8))) void
             my_case = cid;
         }
         const CaseDev &cs = case_const(C, cid);
-        const int kb = ncl == 1 ? 6 : 6 - (32 - __clz(ncl - 1));
-        const int kk = 1 << kb;
-        const int gc = lane >> kb, sub = lane & (kk - 1);
-        const bool own = gc < ncl;
-        const int g = cb + gc;
-        int start = 0, n = 0;
-        double vol = 0.0, scm = 0.0;
-        if (own) {
-            start = C.cstart[g];
-            n = C.cstart[g + 1] - start;
-            vol = C.vol[g];
-            scm = C.sigc[g];
-        }
-        const bool work = own && n <= D;
-        const int nn = work ? n : 0;
-        // nothing to do in a tile without particles of its own (unless trace records are kept)
-        if (!tracing && !__any(nn > 0)) continue;
-        const bool lead = work && sub == 0;
-        const P *vx = Dd.vel[0] + start, *vy = Dd.vel[1] + start, *vz = Dd.vel[2] + start;
 
         // A lane's particles are i = sub, sub + kk, ...; they are read kU at a time with all
         // loads in flight before the first is used, and summed in that order.
         constexpr int kU = 2;
+        const P *vx, *vy, *vz;
+        int kb, kk, sub, nn;
         auto load_u = [&](int i0, P (&bx)[kU], P (&by)[kU], P (&bz)[kU]) {
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
@@ -1740,33 +1726,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8))) void
                 }
             }
         };
-        // Eq. 31: sums of c and |c|^2
-        double s1[4] = {0.0, 0.0, 0.0, 0.0};
-        for (int i0 = sub; i0 < nn; i0 += kU * kk) {
-#pragma clang fp contract(fast)
-            P bx[kU], by[kU], bz[kU];
-            load_u(i0, bx, by, bz);
-#pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                if (i0 + u * kk < nn) {
-                    const double x = (double)bx[u], y = (double)by[u], z = (double)bz[u];
-                    s1[0] = s1[0] + x;
-                    s1[1] = s1[1] + y;
-                    s1[2] = s1[2] + z;
-                    s1[3] = s1[3] + (x * x + y * y + z * z);
-                }
-            }
-        }
-        group_sum<4>(s1, kb);
-        double U[3] = {0.0, 0.0, 0.0};
-        if (nn > 0) {
-#pragma unroll
-            for (int a = 0; a < 3; ++a) U[a] = s1[a] / (double)nn;
-        }
-        // sums of the peculiar |C|^2 and |C|^2 C: always in FP64 (T is their first); in
-        // FP32-mixed (T from the raw sums) only where the heat flux is needed
-        double s2[4] = {0.0, 0.0, 0.0, 0.0};
-        auto peculiar = [&](bool on) {
+        // sums of the peculiar |C|^2 and |C|^2 C about U, over the group
+        auto peculiar = [&](bool on, const double (&U)[3], double (&s2)[4]) {
             if (on) {
                 if constexpr (sizeof(P) == 4) {
                     // FP32 peculiar velocity and products (C = (c - U_f) - (U - U_f))
@@ -1815,12 +1776,112 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8))) void
             }
             group_sum<4>(s2, kb);
         };
-        if constexpr (sizeof(P) == 8) peculiar(nn >= 2);
 
-        TraceDev *tr = (lead && tracing) ? &C.trace[g] : nullptr;
+        // ---- the sums of this tile and of the next ones of the case, as long as their cells fit
+        int m = 0, nb = 0;                 // cells and tiles of the batch
+        while (t < ntiles && nx.ci == cid && nb < kBatch) {
+            const int cb = nx.cb, ncl = nx.ce - cb;
+            if (ncl < 0 || ncl > MAXC || cb < 0 || cb + ncl > NC) {
+                if (lane == 0) raise_error(G, kErrState);
+                return;
+            }
+            if (m + ncl > 64) break;
+            pos += nbx;
+            t = xcd_tile(pos, xcd, csh);
+            nx = tile_ref(C, t, ntiles);
+            if (ncl == 0) continue;        // a tile inside one dense cell
+            kb = ncl == 1 ? 6 : 6 - (32 - __clz(ncl - 1));
+            kk = 1 << kb;
+            sub = lane & (kk - 1);
+            const int gc = lane >> kb, g = cb + gc;
+            const bool own = gc < ncl;
+            int start = 0, n = 0;
+            double vol = 0.0, scm = 0.0;
+            if (own) {
+                start = C.cstart[g];
+                n = C.cstart[g + 1] - start;
+                vol = C.vol[g];
+                scm = C.sigc[g];
+            }
+            const bool work = own && n <= D;
+            nn = work ? n : 0;
+            // nothing to do in a tile without particles of its own (unless trace records are kept)
+            if (!tracing && !__any(nn > 0)) continue;
+            vx = Dd.vel[0] + start;
+            vy = Dd.vel[1] + start;
+            vz = Dd.vel[2] + start;
+            // Eq. 31: sums of c and |c|^2
+            double s1[4] = {0.0, 0.0, 0.0, 0.0};
+            for (int i0 = sub; i0 < nn; i0 += kU * kk) {
+#pragma clang fp contract(fast)
+                P bx[kU], by[kU], bz[kU];
+                load_u(i0, bx, by, bz);
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    if (i0 + u * kk < nn) {
+                        const double x = (double)bx[u], y = (double)by[u], z = (double)bz[u];
+                        s1[0] = s1[0] + x;
+                        s1[1] = s1[1] + y;
+                        s1[2] = s1[2] + z;
+                        s1[3] = s1[3] + (x * x + y * y + z * z);
+                    }
+                }
+            }
+            group_sum<4>(s1, kb);
+            // the peculiar sums: in FP64 always (T is their first); in FP32-mixed (T from the raw
+            // sums) later, where the heat flux is needed
+            double s2[4] = {0.0, 0.0, 0.0, 0.0};
+            if constexpr (sizeof(P) == 8) {
+                double U[3] = {0.0, 0.0, 0.0};
+                if (nn > 0) {
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) U[a] = s1[a] / (double)nn;
+                }
+                peculiar(nn >= 2, U, s2);
+            }
+            if (own && sub == 0) {
+                const int k = m + gc;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    c_s1[j][k] = s1[j];
+                    c_s2[j][k] = s2[j];
+                }
+                c_vol[k] = vol;
+                c_scm[k] = scm;
+                c_cell[k] = g;
+                c_num[k] = work ? n : -1;
+            }
+            if (lane == 0) {
+                b_cb[nb] = cb;
+                b_m0[nb] = m;
+            }
+            m += ncl;
+            ++nb;
+        }
+        if (nb == 0) continue;
+        if (lane == 0) b_m0[nb] = m;
+        team_sync<64>();
+
+        // ---- a lane per cell: the scalars
+        const bool mine = lane < m && c_num[lane] >= 0;
+        const int g = mine ? c_cell[lane] : 0;
+        nn = mine ? c_num[lane] : 0;
+        double s1[4] = {0.0, 0.0, 0.0, 0.0}, s2[4] = {0.0, 0.0, 0.0, 0.0}, U[3] = {0.0, 0.0, 0.0};
+        double vol = 0.0, scm = 0.0;
+        if (nn > 0) {
+            vol = c_vol[lane];
+            scm = c_scm[lane];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                s1[j] = c_s1[j][lane];
+                s2[j] = c_s2[j][lane];
+            }
+#pragma unroll
+            for (int a = 0; a < 3; ++a) U[a] = s1[a] / (double)nn;
+        }
         double T = 0.0, pr = 0.0, p = 0.0, tau = 0.0, dtD = 0.0;
         bool active = false;
-        if (work && nn >= 2) {
+        if (nn >= 2) {
             if constexpr (sizeof(P) == 4)
                 T = gas.m * (s1[3] - (s1[0] * s1[0] + s1[1] * s1[1] + s1[2] * s1[2]) / (double)nn) /
                     (3.0 * kKB * (double)(nn - 1));
@@ -1828,7 +1889,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8))) void
                 T = gas.m * s2[0] / (3.0 * kKB * (double)(nn - 1));
             if (!isfinite(T)) raise_error(G, kErrNumeric);
             active = T > 0.0 && vol > 0.0;
-            if (!active && lead) ++skipped[0];
+            if (!active) ++skipped[0];
         }
         if (active) {
             const double nd = (double)nn * cs.F_N / vol;
@@ -1853,12 +1914,49 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8))) void
             }
             pr = -expm1(-dtS / tau);
         }
-        // Eq. 32 heat flux (needed by the Shakhov target only)
+        // Eq. 32 heat flux (needed by the Shakhov target only): the peculiar sums of the tiles that
+        // hold such a cell, by their lane groups again
         if constexpr (sizeof(P) == 4) {
-            if (__any(pr > 0.0 && nn >= 3)) peculiar(pr > 0.0 && nn >= 3);
+            const unsigned long long need = __ballot(pr > 0.0 && nn >= 3);
+            if (need) {
+                const int nn_l = nn;
+                for (int b = 0; b < nb; ++b) {
+                    const int cb = __builtin_amdgcn_readfirstlane(b_cb[b]);
+                    const int m0 = __builtin_amdgcn_readfirstlane(b_m0[b]);
+                    const int ncl = __builtin_amdgcn_readfirstlane(b_m0[b + 1]) - m0;
+                    const unsigned long long nt = (need >> m0) & (ncl == 64 ? ~0ull : (1ull << ncl) - 1ull);
+                    if (!nt) continue;
+                    kb = ncl == 1 ? 6 : 6 - (32 - __clz(ncl - 1));
+                    kk = 1 << kb;
+                    sub = lane & (kk - 1);
+                    const int gc = lane >> kb;
+                    const bool on = gc < ncl && ((nt >> gc) & 1ull);
+                    const int k = on ? m0 + gc : 0, start = on ? C.cstart[cb + gc] : 0;
+                    nn = on ? c_num[k] : 0;
+                    vx = Dd.vel[0] + start;
+                    vy = Dd.vel[1] + start;
+                    vz = Dd.vel[2] + start;
+                    double Ug[3] = {0.0, 0.0, 0.0}, sg[4] = {0.0, 0.0, 0.0, 0.0};
+                    if (on) {
+#pragma unroll
+                        for (int a = 0; a < 3; ++a) Ug[a] = c_s1[a][k] / (double)nn;
+                    }
+                    peculiar(on, Ug, sg);
+                    if (on && sub == 0) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) c_s2[j][k] = sg[j];
+                    }
+                }
+                nn = nn_l;
+                team_sync<64>();
+                if (pr > 0.0 && nn >= 3) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) s2[j] = c_s2[j][lane];
+                }
+            }
         }
         double Q[3] = {0.0, 0.0, 0.0};
-        if (work && nn >= 3 && vol > 0.0 && (sizeof(P) == 8 || pr > 0.0)) {
+        if (nn >= 3 && vol > 0.0 && (sizeof(P) == 8 || pr > 0.0)) {
             const double nd = (double)nn * cs.F_N / vol;
             const double f = nd * (double)nn / ((double)(nn - 1) * (double)(nn - 2));
             for (int a = 0; a < 3; ++a) Q[a] = f * 0.5 * gas.m * s2[1 + a];
@@ -1876,40 +1974,40 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8))) void
             if (Mu >= 0.0 && Mu < 1e9) ncol = (long long)floor(Mu);
             else raise_error(G, kErrNumeric);
         }
-        if (lead) {
-            if (nn > 0) {                 // the tile kernel reads no record of an empty cell
-                double *R = C.cellrec + (size_t)kRecLen * g;
-                R[kRecU + 0] = U[0];
-                R[kRecU + 1] = U[1];
-                R[kRecU + 2] = U[2];
-                R[kRecT] = T;
-                R[kRecPr] = pr;
-                R[kRecScm] = scm;
-                R[kRecNcol] = (double)ncol;
-                R[kRecAct] = active ? 1.0 : 0.0;
-                if (pr > 0.0) {
-                    R[kRecPar + 0] = Q[0];
-                    R[kRecPar + 1] = Q[1];
-                    R[kRecPar + 2] = Q[2];
-                    R[kRecPar + 3] = p;
-                    R[kRecPar + 4] = gas.R * T;
-                    R[kRecPar + 5] = sqrt(2.0 * gas.R * T);
-                    R[kRecPar + 6] = a_max;
-                }
-            }
-            if (tr) {
-                *tr = TraceDev{};
-                tr->n = nn;
-                for (int a = 0; a < 4; ++a) tr->pre_sum[a] = s1[a];
-                if (active) {
-                    tr->T = T;
-                    tr->tau = tau;
-                    tr->dt_dsmc = dtD;
-                    tr->p_relax = pr;
-                    tr->a_max = pr > 0.0 ? a_max : 0.0;
-                }
+        if (nn > 0) {                     // the tile kernel reads no record of an empty cell
+            double *R = C.cellrec + (size_t)kRecLen * g;
+            R[kRecU + 0] = U[0];
+            R[kRecU + 1] = U[1];
+            R[kRecU + 2] = U[2];
+            R[kRecT] = T;
+            R[kRecPr] = pr;
+            R[kRecScm] = scm;
+            R[kRecNcol] = (double)ncol;
+            R[kRecAct] = active ? 1.0 : 0.0;
+            if (pr > 0.0) {
+                R[kRecPar + 0] = Q[0];
+                R[kRecPar + 1] = Q[1];
+                R[kRecPar + 2] = Q[2];
+                R[kRecPar + 3] = p;
+                R[kRecPar + 4] = gas.R * T;
+                R[kRecPar + 5] = sqrt(2.0 * gas.R * T);
+                R[kRecPar + 6] = a_max;
             }
         }
+        if (tracing && mine) {
+            TraceDev *tr = &C.trace[g];
+            *tr = TraceDev{};
+            tr->n = nn;
+            for (int a = 0; a < 4; ++a) tr->pre_sum[a] = s1[a];
+            if (active) {
+                tr->T = T;
+                tr->tau = tau;
+                tr->dt_dsmc = dtD;
+                tr->p_relax = pr;
+                tr->a_max = pr > 0.0 ? a_max : 0.0;
+            }
+        }
+        team_sync<64>();
     }
     tally_add<1>(C, tally, my_case, HS_CNT_SKIPPED_CELLS, skipped);
     tally_flush<1>(C, tally, HS_CNT_SKIPPED_CELLS);

@@ -218,3 +218,25 @@ def test_ntc_window_dense(gas, ppc, rate):
         assert to["ncol"].max() > 65536
     g, o = sim.export_state(0), ora.get_state(0)
     assert np.abs(g["vel"] - o["v"]).max() <= 1e-12 * np.abs(o["v"]).max()
+
+
+# many tiles a block of the scalars kernel: batches of one case and over the edges of cases, of few
+# and many cells a tile, with empty, dense and heat-carrying cells between
+@pytest.mark.parametrize("blocks", [8, 24])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_scalar_batches(gas, blocks, precision):
+    from paper_2506_23917_amd.hs import Sim
+    cases = [W.sod_1d(seed=5 + k, ncells=nc, ppc_left=ppc, n_steady=0)
+             for k, (nc, ppc) in enumerate([(40, 8), (6, 160), (90, 24), (4, 300), (200, 2), (2, 8)])]
+    cases[2]["adapt_dt"] = True
+    ref = Sim(gas, cases, precision=precision, trace=True, device="cuda:0")
+    sim = Sim(gas, cases, precision=precision, trace=True, device="cuda:0")
+    sim.set_grid("scalars", blocks)
+    for s in (ref, sim):
+        s.step(4)
+    for k in range(len(cases)):
+        a, b = ref.export_state(k), sim.export_state(k)
+        for f in ("id", "cell", "pos", "vel", "acc"):
+            assert np.array_equal(a[f], b[f]), (k, f)
+        assert ref.trace(k).tobytes() == sim.trace(k).tobytes()
+        assert ref.counters(k) == sim.counters(k) and ref.step_dt(k) == sim.step_dt(k)
