@@ -3433,18 +3433,24 @@ void Launch::scatter(const Ctx &c, void *s)
 }
 // Tile kernels loop over tiles with a fixed grid: wide for the streaming gather and scalar
 // kernels; the collision kernel's per-wave setup and counter flush are paid once per block.
+static long long max_tiles(const Ctx &c)
+{
+    return ((long long)c.capacity + 4ll * c.ncells_total) / kTileW + 1;
+}
 static int tile_grid(const Ctx &c, int which, long long cap)
 {
     long long g = c.grid[which];
-    if (g <= 0) {
-        const long long maxtiles = ((long long)c.capacity + 4ll * c.ncells_total) / kTileW + 1;
-        g = std::max(1ll, std::min(maxtiles, cap));
-    }
+    if (g <= 0) g = std::max(1ll, std::min(max_tiles(c), cap));
     return (int)((g + kXcds - 1) / kXcds * kXcds);     // whole blocks per XCD
 }
 void Launch::gather(const Ctx &c, void *s)
 {
-    const int g = tile_grid(c, HS_KERNEL_GATHER, 256ll * 32);
+    // 8192 blocks fill the chip (eight waves a SIMD).  A batch of many tiles runs on 6144, which
+    // leave the dense kernel beside it a place and end more evenly (800 x 600 cylinder, us a step:
+    // 960 at 8192, 944 at 6144, 942 at 4096); with fewer tiles a block the last round counts for
+    // more (eight jets, 34k tiles of capacity: 196 at 8192, 199 at 6144; 800 x 600 at half the
+    // particles, 52k: 494 and 497; 640 x 480, 63k: 606 and 604)
+    const int g = tile_grid(c, HS_KERNEL_GATHER, max_tiles(c) > 256ll * 256 ? 256ll * 24 : 256ll * 32);
     if (c.precision == HS_FP64) hipLaunchKernelGGL((k_sort_gather<double, kTileW, kCapWave>), dim3(g), dim3(64), 0, S_(s), c);
     else hipLaunchKernelGGL((k_sort_gather<float, kTileW, kCapWave>), dim3(g), dim3(64), 0, S_(s), c);
 }
@@ -3456,14 +3462,15 @@ void Launch::scalars(const Ctx &c, void *s)
 }
 void Launch::collide(const Ctx &c, void *s)
 {
-    // tiles differ in length (their NTC rounds and acceptance-rejection draws): 8192 blocks, a few
-    // tiles each, keep the chip even (FP64 332 x 249 cylinder, us a step: 745 at 1024 blocks, 600
-    // at 4096, 550 at 8192 and 16384; FP32 sphere 759 at 4096, 741 at 8192, 800 x 600 cylinder 977
-    // and 969)
+    // tiles differ in length (their NTC rounds and acceptance-rejection draws): FP64 8192 blocks, a
+    // few tiles each, keep the chip even (332 x 249 cylinder, us a step: 745 at 1024 blocks, 600 at
+    // 4096, 550 at 8192 and 16384); FP32 24576, six rounds of the 4096 that fit the chip (us a step:
+    // 96 x 64 x 64 sphere 755 at 4096, 732 at 8192, 718 at 12288, 698-700 at 20480 and 24576, 707 at
+    // 40960; 800 x 600 cylinder 968, 948, 943, 930, 944; jets and O-grids the same at all of them)
     if (c.precision == HS_FP64)
         hipLaunchKernelGGL(k_collide_tile_f64, dim3(tile_grid(c, HS_KERNEL_COLLIDE, 256ll * 32)), dim3(64), 0, S_(s), c);
     else
-        hipLaunchKernelGGL(k_collide_tile_f32, dim3(tile_grid(c, HS_KERNEL_COLLIDE, 256ll * 32)), dim3(64), 0, S_(s), c);
+        hipLaunchKernelGGL(k_collide_tile_f32, dim3(tile_grid(c, HS_KERNEL_COLLIDE, 256ll * 96)), dim3(64), 0, S_(s), c);
 }
 void Launch::dense(const Ctx &c, void *s)
 {
