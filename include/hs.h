@@ -203,7 +203,10 @@ hs_status hs_plan(const hs_gas *gas, const hs_case *cases, int n_cases, hs_preci
  * volumes, draw the initial particles (uniform positions in each cell's fluid part,
  * velocities U + Eq. 17 Maxwellian, N = floor(n V / F_N + u) per cell, ids in cell order)
  * and set (sigma_T c_r)_max.  dev_workspace: device pointer to >= hs_plan() bytes, owned
- * by the caller.  hip_stream: the hipStream_t to use.  On success *out is a new sim. */
+ * by the caller.  hip_stream: the hipStream_t to use.  On success *out is a new sim.
+ * The sim owns a second stream of its own (unless HS_FLAG_GRAPH is set, chosen by a probe of
+ * about 0.15 ms that runs beside hip_stream), and up to 8 MB of page-locked host memory,
+ * allocated at the first read of fields to the host; both go with hs_destroy. */
 hs_status hs_init_particles(const hs_gas *gas, const hs_case *cases, int n_cases,
                             hs_precision prec, uint32_t flags, void *dev_workspace,
                             size_t dev_bytes, void *hip_stream, hs_sim **out);
