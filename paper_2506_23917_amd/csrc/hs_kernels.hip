@@ -1287,6 +1287,20 @@ __device__ __forceinline__ int chunk_shift(int ntiles)
     const int per = ntiles / (8 * kXcds);
     return per < 1 ? 0 : min(kTileChunkShift, 31 - __clz(per));
 }
+// Parts (2^part_shift) that the collision kernel deals a tile's cells out in, a wave to a part.  In
+// a batch of few tiles the chip waits for the longest of them, a serial chain of NTC rounds and
+// Shakhov draws; the parts' chains are shorter and run side by side.  Lane groups are those of the
+// whole tile (a part leaves the other groups idle), so a cell's sums keep their order bit for bit,
+// at any number of parts.  Four parts up to 512 tiles, two up to 2048 (about two waves a SIMD), one
+// above.  Steps in us, whole tiles against parts: FP64 18k-particle tube (75 tiles) 119 -> 94, 80 x
+// 60 cylinder (284) 190 -> 150, in FP32 143 -> 124, restart box (650) 76 -> 70 (four parts 77), 0-D
+// 1999 x 150 (1203) 148 -> 112, 160 x 120 cylinder at 20 a cell (1800) 221 -> 218, FP32 170 -> 163;
+// eight parts up to 512 tiles 95, 153.
+constexpr int kPartTiles2 = 2048, kPartTiles4 = 512;
+__device__ __forceinline__ int part_shift(int ntiles)
+{
+    return ntiles <= kPartTiles4 ? 2 : ntiles <= kPartTiles2 ? 1 : 0;
+}
 // FP32-mixed tiles of the tile collision kernel with more cells than this send their Step (5)
 // sums in address order (see the kernel); fewer, wider groups send their own.  FP64 tiles always
 // send their own: that kernel runs two waves per SIMD and is bound by instruction issue, its
@@ -2019,7 +2033,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5, 8))) void
 // state) staged in LDS and the cell scalars from k_cell_scalars.  Cells are served by lane
 // groups as in k_cell_scalars; after the NTC every lane reads and writes only its own
 // particles.
-template <typename P, int TW, int D>
+template <typename P, int TW, int D, bool PARTS>
 __device__ __forceinline__ void collide_tile_body(const Ctx &C)
 {
     constexpr int MAXC = TW / 4;
@@ -2060,15 +2074,18 @@ __device__ __forceinline__ void collide_tile_body(const Ctx &C)
     int my_case = -1;
 
     const int xcd = blockIdx.x % kXcds, nbx = gridDim.x / kXcds;
-    const int csh = chunk_shift(ntiles);
+    // parts of tiles: part k & (2^psh - 1) of tile k >> psh
+    const int psh = PARTS ? part_shift(ntiles) : 0, nitems = ntiles << psh;
+    const int csh = chunk_shift(nitems);
     int pos = blockIdx.x / kXcds;
     int t = xcd_tile(pos, xcd, csh);
-    TileRef nx = tile_ref(C, t, ntiles);
-    while (t < ntiles) {
+    TileRef nx = tile_ref(C, t >> psh, ntiles);
+    while (t < nitems) {
         const TileRef cur = nx;
+        const int part = t & ((1 << psh) - 1);
         pos += nbx;
         t = xcd_tile(pos, xcd, csh);
-        nx = tile_ref(C, t, ntiles);
+        nx = tile_ref(C, t >> psh, ntiles);
         const int cb = cur.cb;
         const int ncl = cur.ce - cb;
         const int cid = cur.ci;
@@ -2101,6 +2118,16 @@ __device__ __forceinline__ void collide_tile_body(const Ctx &C)
         const int incl = wave_incl_scan(nn0);
         const int np = wave_last(incl);
         if (np == 0) continue;           // empty cells only (or dense ones, served elsewhere)
+        // the part's cells: those whose middle particle lies in its share of the tile's, a run of
+        // cells, and their run of slots
+        unsigned long long pcells = ~0ull;
+        int p_lo = 0, p_hi = np;
+        if constexpr (PARTS) {
+            pcells = __ballot(nn0 > 0 && ((2 * incl - nn0) << psh) / (2 * np) == part);
+            if (pcells == 0ull) continue;
+            p_lo = __builtin_amdgcn_readlane(incl - nn0, __ffsll((long long)pcells) - 1);
+            p_hi = __builtin_amdgcn_readlane(incl, 63 - __clzll((long long)pcells));
+        }
         // without a dense cell the tile's slots are the contiguous run of the sorted state that
         // starts at its first cell (nearly every tile); else a slot's cell is searched for
         const bool contig = !__any(lane < ncl && n_lane > D);
@@ -2116,7 +2143,7 @@ __device__ __forceinline__ void collide_tile_body(const Ctx &C)
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     const int s = lane + 64 * r;
-                    if (s < np) {
+                    if ((!PARTS || s >= p_lo) && s < p_hi) {
                         uint32_t i = (uint32_t)(base0 + s);
                         if (!contig) {
                             int a = 0, b = ncl - 1;
@@ -2140,7 +2167,7 @@ __device__ __forceinline__ void collide_tile_body(const Ctx &C)
                 for (int r = 0; r < R; ++r) {
                     const int s = lane + 64 * r;
                     boff[r] = 0;
-                    if (s < np) {
+                    if ((!PARTS || s >= p_lo) && s < p_hi) {
                         int i = base0 + s;
                         if (!contig) {
                             int a = 0, b = ncl - 1;
@@ -2157,7 +2184,7 @@ __device__ __forceinline__ void collide_tile_body(const Ctx &C)
                 P gv[R][3];
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    if (lane + 64 * r < np) {
+                    if ((!PARTS || lane + 64 * r >= p_lo) && lane + 64 * r < p_hi) {
 #pragma unroll
                         for (int c = 0; c < 3; ++c) gv[r][c] = ld_off(Dd.vel[c], boff[r]);
                     }
@@ -2165,7 +2192,7 @@ __device__ __forceinline__ void collide_tile_body(const Ctx &C)
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     const int s = lane + 64 * r;
-                    if (s < np) {
+                    if ((!PARTS || s >= p_lo) && s < p_hi) {
                         s_v[0][s] = gv[r][0];
                         s_v[1][s] = gv[r][1];
                         s_v[2][s] = gv[r][2];
@@ -2218,7 +2245,7 @@ __device__ __forceinline__ void collide_tile_body(const Ctx &C)
         }
         if (goff != 0xFF) s_gcell[goff] = (uint8_t)lane;
         if (lane < ncl) {
-            c_goff[lane] = (uint8_t)goff;                              // 0xFF: no group
+            c_goff[lane] = (uint8_t)(!PARTS || ((pcells >> lane) & 1ull) ? goff : 0xFF);   // 0xFF: no sums here
             c_kb[lane] = 0;
         }
         team_sync<64>();
@@ -2244,7 +2271,7 @@ __device__ __forceinline__ void collide_tile_body(const Ctx &C)
         if constexpr (sizeof(P) == 4) __builtin_amdgcn_s_waitcnt(0x0F70);    // vmcnt(0)
         team_sync<64>();
         const int cn = __shfl(n_lane, gc & 63, 64);
-        const bool work = own && cn <= D;
+        const bool work = own && cn <= D && (!PARTS || ((pcells >> gc) & 1ull));
         if (!work) {
             active = false;
             ncol = 0;
@@ -2636,11 +2663,20 @@ constexpr int kTileW = 256;         // tile weight: particles + 4 per cell
 // FP32-mixed: registers capped for four waves per SIMD (the LDS tile allows four).
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_collide_tile_f32(Ctx C)
 {
-    collide_tile_body<float, kTileW, kCapWave>(C);
+    collide_tile_body<float, kTileW, kCapWave, false>(C);
 }
 __global__ __launch_bounds__(64) void k_collide_tile_f64(Ctx C)
 {
-    collide_tile_body<double, kTileW, kCapWave>(C);
+    collide_tile_body<double, kTileW, kCapWave, false>(C);
+}
+// the same for batches of few tiles, dealt out in parts
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_collide_parts_f32(Ctx C)
+{
+    collide_tile_body<float, kTileW, kCapWave, true>(C);
+}
+__global__ __launch_bounds__(64) void k_collide_parts_f64(Ctx C)
+{
+    collide_tile_body<double, kTileW, kCapWave, true>(C);
 }
 
 // Sort `a[0..p2)` ascending in LDS with a bitonic network (p2 a power of two).
@@ -3437,10 +3473,10 @@ static long long max_tiles(const Ctx &c)
 {
     return ((long long)c.capacity + 4ll * c.ncells_total) / kTileW + 1;
 }
-static int tile_grid(const Ctx &c, int which, long long cap)
+static int tile_grid(const Ctx &c, int which, long long cap, int parts = 1)
 {
     long long g = c.grid[which];
-    if (g <= 0) g = std::max(1ll, std::min(max_tiles(c), cap));
+    if (g <= 0) g = std::max(1ll, std::min(max_tiles(c) * parts, cap));
     return (int)((g + kXcds - 1) / kXcds * kXcds);     // whole blocks per XCD
 }
 void Launch::gather(const Ctx &c, void *s)
@@ -3467,10 +3503,21 @@ void Launch::collide(const Ctx &c, void *s)
     // 4096, 550 at 8192 and 16384); FP32 24576, six rounds of the 4096 that fit the chip (us a step:
     // 96 x 64 x 64 sphere 755 at 4096, 732 at 8192, 718 at 12288, 698-700 at 20480 and 24576, 707 at
     // 40960; 800 x 600 cylinder 968, 948, 943, 930, 944; jets and O-grids the same at all of them)
-    if (c.precision == HS_FP64)
-        hipLaunchKernelGGL(k_collide_tile_f64, dim3(tile_grid(c, HS_KERNEL_COLLIDE, 256ll * 32)), dim3(64), 0, S_(s), c);
-    else
-        hipLaunchKernelGGL(k_collide_tile_f32, dim3(tile_grid(c, HS_KERNEL_COLLIDE, 256ll * 96)), dim3(64), 0, S_(s), c);
+    // Batches that can come down to few tiles (a capacity is often 1.6 times the live particles) take
+    // the kernels that deal tiles out in parts; the others' kernels leave the code for it out, which
+    // cost the FP32 one 0.5-1.5% (800 x 600 cylinder 903 -> 907 us, jets 196 -> 197, 240 x 180
+    // cylinder of 3900 tiles of capacity 179 -> 182).  No more blocks than parts: eight times the
+    // tiles of an all-dense 0-D batch (1024 x 1000) took 187 us instead of 171.
+    const bool parts = max_tiles(c) <= kPartTiles2 * 3 / 2;
+    const long long cap = parts ? 2 * kPartTiles2 : c.precision == HS_FP64 ? 256ll * 32 : 256ll * 96;
+    const dim3 grid(tile_grid(c, HS_KERNEL_COLLIDE, cap, parts ? 4 : 1));
+    if (c.precision == HS_FP64) {
+        if (parts) hipLaunchKernelGGL(k_collide_parts_f64, grid, dim3(64), 0, S_(s), c);
+        else hipLaunchKernelGGL(k_collide_tile_f64, grid, dim3(64), 0, S_(s), c);
+    } else {
+        if (parts) hipLaunchKernelGGL(k_collide_parts_f32, grid, dim3(64), 0, S_(s), c);
+        else hipLaunchKernelGGL(k_collide_tile_f32, grid, dim3(64), 0, S_(s), c);
+    }
 }
 void Launch::dense(const Ctx &c, void *s)
 {

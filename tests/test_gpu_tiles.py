@@ -240,3 +240,24 @@ def test_scalar_batches(gas, blocks, precision):
             assert np.array_equal(a[f], b[f]), (k, f)
         assert ref.trace(k).tobytes() == sim.trace(k).tobytes()
         assert ref.counters(k) == sim.counters(k) and ref.step_dt(k) == sim.step_dt(k)
+
+
+# tiles dealt out in four and two parts (up to 512 and 2048 tiles) and whole: the same bits for a case
+# in batches of each size, with few and many cells a tile, empty, dense and heat-carrying cells
+@pytest.mark.parametrize("filler", [1500, 9000])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_tile_parts(gas, filler, precision):
+    from paper_2506_23917_amd.hs import Sim
+    cases = [W.sod_1d(seed=5 + k, ncells=nc, ppc_left=ppc, n_steady=1)
+             for k, (nc, ppc) in enumerate([(40, 8), (6, 160), (90, 24), (4, 300), (200, 2), (2, 8)])]
+    cases[2]["adapt_dt"] = True
+    ref = Sim(gas, cases + [W.sod_1d(seed=99, ncells=filler)], precision=precision, trace=True, device="cuda:0")
+    sim = Sim(gas, cases, precision=precision, trace=True, device="cuda:0")
+    for s in (ref, sim):
+        s.step(4)
+    for k in range(len(cases)):
+        a, b = ref.export_state(k), sim.export_state(k)
+        for f in ("id", "cell", "pos", "vel", "acc"):
+            assert np.array_equal(a[f], b[f]), (k, f)
+        assert ref.trace(k).tobytes() == sim.trace(k).tobytes()
+        assert ref.counters(k) == sim.counters(k) and ref.step_dt(k) == sim.step_dt(k)
