@@ -1355,8 +1355,10 @@ enum : int {
 // particles; cells denser than D go to k_collide_dense.  This kernel restores the stable
 // order of each cell's particles (source order) and writes the sorted state.  Its time is
 // load latency: in FP32 it runs at eight waves per SIMD (64 VGPRs, a few spilled), in FP64
-// at four (eight would spill 32 VGPRs).
-template <typename P, int TW, int D>
+// at four (eight would spill 32 VGPRs).  In batches of few tiles (PARTS) a tile's cells are dealt
+// out as in the collision kernel: FP64 80 x 60 cylinder 150 -> 143 us a step, in FP32 124 -> 119, 160 x
+// 120 at 20 a cell 219 -> 210 and 164 -> 156, 0-D batch of 1999 x 150 112 -> 110, tube 94 -> 93.
+template <typename P, int TW, int D, bool PARTS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(P) == 4 ? 8 : 4, 8))) void k_sort_gather(Ctx C)
 {
     constexpr int MAXC = TW / 4;
@@ -1383,15 +1385,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(P) ==
     const int NC = C.ncells_total;
 
     const int xcd = blockIdx.x % kXcds, nbx = gridDim.x / kXcds;
-    const int csh = chunk_shift(ntiles);
+    const int psh = PARTS ? part_shift(ntiles) : 0, nitems = ntiles << psh;
+    const int csh = chunk_shift(nitems);
     int pos = blockIdx.x / kXcds;
     int t = xcd_tile(pos, xcd, csh);
-    TileRef nx = tile_ref(C, t, ntiles);
-    while (t < ntiles) {
+    TileRef nx = tile_ref(C, t >> psh, ntiles);
+    while (t < nitems) {
         const TileRef cur = nx;
+        const int part = t & ((1 << psh) - 1);
         pos += nbx;
         t = xcd_tile(pos, xcd, csh);
-        nx = tile_ref(C, t, ntiles);
+        nx = tile_ref(C, t >> psh, ntiles);
         const int cb = cur.cb;
         const int ncl = cur.ce - cb;
         if (ncl < 0 || ncl > MAXC || cb < 0 || cb + ncl > NC || cur.ci < 0 || cur.ci >= C.n_cases) {
@@ -1410,10 +1414,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(P) ==
             dense = n > D;
             c_start[lane] = start;
         }
-        const int nn = (own && !dense) ? n : 0;
+        int nn = (own && !dense) ? n : 0;
         const int incl = wave_incl_scan(nn);
-        const int off = incl - nn;
-        const int np = wave_last(incl);
+        int off = incl - nn;
+        int np = wave_last(incl);
+        if constexpr (PARTS) {
+            // the cells of the part (a run of the tile's, as in the collision kernel) and no others
+            if (np == 0) continue;
+            const bool in = nn > 0 && ((2 * incl - nn) << psh) / (2 * np) == part;
+            const unsigned long long pcells = __ballot(in);
+            if (pcells == 0ull) continue;
+            const int lo = __builtin_amdgcn_readlane(off, __ffsll((long long)pcells) - 1);
+            np = __builtin_amdgcn_readlane(incl, 63 - __clzll((long long)pcells)) - lo;
+            off = min(max(off - lo, 0), np);
+            if (!in) nn = 0;
+        }
         if (own) c_off[lane] = off;
         if (lane == 0) c_off[ncl] = np;
         if (lane < RW) s_first[lane] = 0ull;
@@ -3473,6 +3488,12 @@ static long long max_tiles(const Ctx &c)
 {
     return ((long long)c.capacity + 4ll * c.ncells_total) / kTileW + 1;
 }
+// Batches that can come down to few tiles (a capacity is often 1.6 times the live particles) take
+// the kernels that deal tiles out in parts; the others' kernels leave the code for it out, which
+// cost the FP32 one 0.5-1.5% (800 x 600 cylinder 903 -> 907 us, jets 196 -> 197, 240 x 180
+// cylinder of 3900 tiles of capacity 179 -> 182).  No more blocks than parts: eight times the
+// tiles of an all-dense 0-D batch (1024 x 1000) took 187 us instead of 171.
+static bool in_parts(const Ctx &c) { return max_tiles(c) <= kPartTiles2 * 3 / 2; }
 static int tile_grid(const Ctx &c, int which, long long cap, int parts = 1)
 {
     long long g = c.grid[which];
@@ -3486,9 +3507,16 @@ void Launch::gather(const Ctx &c, void *s)
     // 960 at 8192, 944 at 6144, 942 at 4096); with fewer tiles a block the last round counts for
     // more (eight jets, 34k tiles of capacity: 196 at 8192, 199 at 6144; 800 x 600 at half the
     // particles, 52k: 494 and 497; 640 x 480, 63k: 606 and 604)
-    const int g = tile_grid(c, HS_KERNEL_GATHER, max_tiles(c) > 256ll * 256 ? 256ll * 24 : 256ll * 32);
-    if (c.precision == HS_FP64) hipLaunchKernelGGL((k_sort_gather<double, kTileW, kCapWave>), dim3(g), dim3(64), 0, S_(s), c);
-    else hipLaunchKernelGGL((k_sort_gather<float, kTileW, kCapWave>), dim3(g), dim3(64), 0, S_(s), c);
+    const bool parts = in_parts(c);
+    const int g = tile_grid(c, HS_KERNEL_GATHER, parts ? 2 * kPartTiles2 : max_tiles(c) > 256ll * 256 ? 256ll * 24 : 256ll * 32, parts ? 4 : 1);
+    const dim3 grid(g), block(64);
+    if (c.precision == HS_FP64) {
+        if (parts) hipLaunchKernelGGL((k_sort_gather<double, kTileW, kCapWave, true>), grid, block, 0, S_(s), c);
+        else hipLaunchKernelGGL((k_sort_gather<double, kTileW, kCapWave, false>), grid, block, 0, S_(s), c);
+    } else {
+        if (parts) hipLaunchKernelGGL((k_sort_gather<float, kTileW, kCapWave, true>), grid, block, 0, S_(s), c);
+        else hipLaunchKernelGGL((k_sort_gather<float, kTileW, kCapWave, false>), grid, block, 0, S_(s), c);
+    }
 }
 void Launch::scalars(const Ctx &c, void *s)
 {
@@ -3503,12 +3531,7 @@ void Launch::collide(const Ctx &c, void *s)
     // 4096, 550 at 8192 and 16384); FP32 24576, six rounds of the 4096 that fit the chip (us a step:
     // 96 x 64 x 64 sphere 755 at 4096, 732 at 8192, 718 at 12288, 698-700 at 20480 and 24576, 707 at
     // 40960; 800 x 600 cylinder 968, 948, 943, 930, 944; jets and O-grids the same at all of them)
-    // Batches that can come down to few tiles (a capacity is often 1.6 times the live particles) take
-    // the kernels that deal tiles out in parts; the others' kernels leave the code for it out, which
-    // cost the FP32 one 0.5-1.5% (800 x 600 cylinder 903 -> 907 us, jets 196 -> 197, 240 x 180
-    // cylinder of 3900 tiles of capacity 179 -> 182).  No more blocks than parts: eight times the
-    // tiles of an all-dense 0-D batch (1024 x 1000) took 187 us instead of 171.
-    const bool parts = max_tiles(c) <= kPartTiles2 * 3 / 2;
+    const bool parts = in_parts(c);
     const long long cap = parts ? 2 * kPartTiles2 : c.precision == HS_FP64 ? 256ll * 32 : 256ll * 96;
     const dim3 grid(tile_grid(c, HS_KERNEL_COLLIDE, cap, parts ? 4 : 1));
     if (c.precision == HS_FP64) {
