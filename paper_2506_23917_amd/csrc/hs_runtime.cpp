@@ -864,8 +864,8 @@ namespace {
 // the tile kernels a step of the 800 x 600 cylinder took 1179 us instead of 1067, of three O-grids
 // 565 instead of 467, in four of ten sims of a process.  So candidate streams are tried, each
 // kept while the next is made (it then gets another queue), until one overlaps with `main`; if
-// none does the last stands.  A sim that replays a graph takes the first: the graph's branches
-// get streams of the runtime's own.
+// none does, or no further one can be made, the last stands.  A sim that replays a graph takes the
+// first: the graph's branches get streams of the runtime's own.
 hipError_t create_side_stream(hipStream_t main, bool probe, unsigned long long *stamps, hipStream_t *side)
 {
     constexpr int kTries = 4;
@@ -874,7 +874,13 @@ hipError_t create_side_stream(hipStream_t main, bool probe, unsigned long long *
     hipError_t e = hipSuccess;
     for (;;) {
         e = hipStreamCreateWithFlags(&tried[n], hipStreamNonBlocking);
-        if (e != hipSuccess) break;
+        if (e != hipSuccess) {
+            if (n > 0) {
+                (void)hipGetLastError();
+                e = hipSuccess;
+            }
+            break;
+        }
         ++n;
         if (!probe || n == kTries) break;
         launch_queue_probe((void *)main, (void *)tried[n - 1], stamps);
