@@ -641,6 +641,8 @@ struct hs_sim {
     // first read of fields, never by a sim on the static scratch array
     char *stage = nullptr;
     size_t stage_half = 0;
+    // made with the sim: an event belongs to the device that is current when it is made, which
+    // at a read may be another one than the stream's
     hipEvent_t ev_stage[2] = {};
     bool stage_tried = false;
 };
@@ -685,13 +687,10 @@ void make_stage(hs_sim *s)
     for (const auto &c : s->plan.cases) most = std::max(most, 8 * 8 * (size_t)c.ncells);
     const size_t half = std::min(kStageHalf, align256(most));
     void *p = nullptr;
-    hipError_t e = hipHostMalloc(&p, 2 * half, hipHostMallocDefault);
-    for (int k = 0; k < 2 && e == hipSuccess; ++k) e = hipEventCreateWithFlags(&s->ev_stage[k], hipEventDisableTiming);
-    if (e == hipSuccess) {
+    if (hipHostMalloc(&p, 2 * half, hipHostMallocDefault) == hipSuccess) {
         s->stage = (char *)p;
         s->stage_half = half;
     } else {
-        if (p) (void)hipHostFree(p);
         (void)hipGetLastError();           // fields are then copied straight to the caller
     }
 }
@@ -1039,11 +1038,12 @@ hs_status create_sim(const hs_gas *gas, const hs_case *cases, int n_cases, hs_pr
     if (side_stream) {
         if (e == hipSuccess)
             e = create_side_stream(s->stream, !(flags & HS_FLAG_GRAPH), (unsigned long long *)at(s, L.out), &s->side);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&s->ev_fork, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&s->ev_join, hipEventDisableTiming);
+        for (hipEvent_t *ev : {&s->ev_fork, &s->ev_join, &s->ev_stage[0], &s->ev_stage[1]})
+            if (e == hipSuccess) e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
     }
     if (e != hipSuccess) {
-        if (s->ev_fork) (void)hipEventDestroy(s->ev_fork);
+        for (hipEvent_t ev : {s->ev_fork, s->ev_join, s->ev_stage[0], s->ev_stage[1]})
+            if (ev) (void)hipEventDestroy(ev);
         if (s->side) (void)hipStreamDestroy(s->side);
         delete s;
         return HS_ERR_DEVICE;

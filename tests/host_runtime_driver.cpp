@@ -268,11 +268,23 @@ void side_stream()
     g_overlap = true;
 }
 
+// Steps and reads of a sim while another device is the thread's current one.
+void other_device()
+{
+    Fixture f(2, 300, 1);
+    CHECK(f.made == HS_OK);
+    g_device = 0;
+    for (int k = 0; k < 3; ++k) {
+        CHECK(hs_step(f.sim, 1) == HS_OK);
+        for (int c = 0; c < 2; ++c) CHECK(read_fields(f.sim, c) == HS_OK);
+    }
+}
+
 struct Named {
     const char *name;
     void (*run)();
 };
-const Named kChecks[] = {{"side_stream", side_stream}};
+const Named kChecks[] = {{"side_stream", side_stream}, {"other_device", other_device}};
 
 }  // namespace
 
