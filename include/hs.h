@@ -205,7 +205,7 @@ hs_status hs_plan(const hs_gas *gas, const hs_case *cases, int n_cases, hs_preci
  * and set (sigma_T c_r)_max.  dev_workspace: device pointer to >= hs_plan() bytes, owned
  * by the caller.  hip_stream: the hipStream_t to use.  On success *out is a new sim.
  * The sim owns a second stream of its own (unless HS_FLAG_GRAPH is set, chosen by a probe of
- * about 0.15 ms that runs beside hip_stream), and up to 8 MB of page-locked host memory,
+ * about 0.15 ms that runs beside hip_stream), and up to 896 KB of page-locked host memory,
  * allocated at the first read of fields to the host; both go with hs_destroy. */
 hs_status hs_init_particles(const hs_gas *gas, const hs_case *cases, int n_cases,
                             hs_precision prec, uint32_t flags, void *dev_workspace,

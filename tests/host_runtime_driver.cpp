@@ -25,7 +25,8 @@ struct FakeEvent {
 
 int g_device = 0;              // the calling thread's current device
 int g_streams = 0, g_events = 0, g_pinned = 0;       // alive
-int g_streams_made = 0, g_pinned_made = 0;
+int g_streams_made = 0;
+size_t g_pinned_bytes = 0;    // page-locked so far
 int g_fail_stream = -1;        // number of the stream whose creation fails
 bool g_overlap = true;         // what the probe of a side stream sees
 bool g_no_memory = false;      // operator new throws
@@ -112,7 +113,7 @@ hipError_t hipHostMalloc(void **p, size_t n, unsigned)
 {
     *p = std::malloc(n);
     ++g_pinned;
-    ++g_pinned_made;
+    g_pinned_bytes += n;
     return hipSuccess;
 }
 hipError_t hipHostFree(void *p)
@@ -280,11 +281,24 @@ void other_device()
     }
 }
 
+// What a program that reads a sim once pays for: page-locking a megabyte or more costs more than it saves.
+void first_read()
+{
+    for (const int ncells : {200, 10080, 100000}) {
+        g_pinned_bytes = 0;
+        Fixture f(2, ncells);
+        CHECK(g_pinned_bytes == 0);
+        for (int k = 0; k < 2; ++k)
+            for (int c = 0; c < 2; ++c) CHECK(read_fields(f.sim, c) == HS_OK);
+        CHECK(g_pinned_bytes < 1000000);
+    }
+}
+
 struct Named {
     const char *name;
     void (*run)();
 };
-const Named kChecks[] = {{"side_stream", side_stream}, {"other_device", other_device}};
+const Named kChecks[] = {{"side_stream", side_stream}, {"other_device", other_device}, {"first_read", first_read}};
 
 }  // namespace
 
