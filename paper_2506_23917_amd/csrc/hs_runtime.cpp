@@ -637,6 +637,7 @@ struct hs_sim {
     };
     std::vector<StepEvents> events;      // one record per timed step
     int64_t timed_steps = 0;
+    std::vector<char> head;              // host copy of the globals and the counters after them (hs_counters)
     // page-locked host memory that fields are read through, in two halves (copy_out); made at the
     // first read of fields, never by a sim on the static scratch array
     char *stage = nullptr;
@@ -709,32 +710,34 @@ struct CopyPart {
 // Copies device arrays to pageable host memory after the stream's work, and waits: through
 // page-locked memory, one half filled by the copy engine while the other is emptied (a copy into
 // fresh pageable memory locks and unlocks it page by page).
-hs_status copy_out(hs_sim *s, const CopyPart *part, int n)
+template <int N>
+hs_status copy_out(hs_sim *s, const CopyPart (&part)[N])
 {
     if (!s->stage_tried) make_stage(s);
     if (!s->stage) {
-        for (int k = 0; k < n; ++k)
-            if (part[k].bytes) HIPCHK(s, hipMemcpyAsync(part[k].to, part[k].from, part[k].bytes, hipMemcpyDeviceToHost, s->stream));
+        for (const CopyPart &p : part)
+            if (p.bytes) HIPCHK(s, hipMemcpyAsync(p.to, p.from, p.bytes, hipMemcpyDeviceToHost, s->stream));
         HIPCHK(s, hipStreamSynchronize(s->stream));
         return HS_OK;
     }
-    std::vector<CopyPart> held[2];         // pieces on their way through each half
+    CopyPart held[2][N];                   // pieces on their way through each half, one of a part at most
+    int n_held[2] = {0, 0};
     auto drain = [&](int h) -> hipError_t {
-        if (held[h].empty()) return hipSuccess;
+        if (n_held[h] == 0) return hipSuccess;
         const hipError_t e = hipEventSynchronize(s->ev_stage[h]);
         if (e != hipSuccess) return e;
-        for (const CopyPart &c : held[h]) std::memcpy(c.to, c.from, c.bytes);
-        held[h].clear();
+        for (int k = 0; k < n_held[h]; ++k) std::memcpy(held[h][k].to, held[h][k].from, held[h][k].bytes);
+        n_held[h] = 0;
         return hipSuccess;
     };
     int h = 0;
     size_t used = 0;
-    for (int k = 0; k < n; ++k) {
-        for (size_t done = 0; done < part[k].bytes;) {
-            const size_t take = std::min(part[k].bytes - done, s->stage_half - used);
+    for (const CopyPart &p : part) {
+        for (size_t done = 0; done < p.bytes;) {
+            const size_t take = std::min(p.bytes - done, s->stage_half - used);
             char *via = s->stage + h * s->stage_half + used;
-            HIPCHK(s, hipMemcpyAsync(via, (const char *)part[k].from + done, take, hipMemcpyDeviceToHost, s->stream));
-            held[h].push_back({(char *)part[k].to + done, via, take});
+            HIPCHK(s, hipMemcpyAsync(via, (const char *)p.from + done, take, hipMemcpyDeviceToHost, s->stream));
+            held[h][n_held[h]++] = {(char *)p.to + done, via, take};
             done += take;
             used += take;
             if (used == s->stage_half) {
@@ -931,6 +934,7 @@ hs_status create_sim(const hs_gas *gas, const hs_case *cases, int n_cases, hs_pr
         return scratch && scratch_bytes < need_scratch ? HS_ERR_CAPACITY : HS_ERR_ARG;
     }
     s->cases.assign(cases, cases + n_cases);
+    s->head.resize(s->lay.cases - s->lay.globals);
     const Layout &L = s->lay;
     Ctx &c = s->ctx;
     std::memset(&c, 0, sizeof(c));
@@ -1219,10 +1223,10 @@ hs_status hs_sample_moments(hs_sim *s, int c, int mode, double *n, double *u3, d
                               {T, out + 4 * nc, T ? 8 * nc : 0},
                               {q3, out + 5 * nc, q3 ? 8 * 3 * nc : 0}};
     if (n && u3 == n + nc && T == n + 4 * nc && q3 == n + 5 * nc) {
-        const CopyPart all{n, out, 8 * 8 * nc};
-        st = copy_out(s, &all, 1);
+        const CopyPart all[1] = {{n, out, 8 * 8 * nc}};
+        st = copy_out(s, all);
     } else {
-        st = copy_out(s, part, 4);
+        st = copy_out(s, part);
     }
     if (st) return st;
     if (n_samples) *n_samples = G.n_samples[c];
@@ -1455,9 +1459,9 @@ hs_status hs_counters(hs_sim *s, int c, int64_t *out)
     // one copy for the globals and the counters that follow them, up to the case's
     constexpr size_t words = sizeof(long long) * kCntCase;
     const size_t first = s->lay.counters - s->lay.globals + words * (size_t)c;
-    std::vector<char> buf(first + words);
+    std::vector<char> &buf = s->head;
     HIPCHK(s, hipStreamSynchronize(s->stream));
-    HIPCHK(s, hipMemcpy(buf.data(), at(s, s->lay.globals), buf.size(), hipMemcpyDeviceToHost));
+    HIPCHK(s, hipMemcpy(buf.data(), at(s, s->lay.globals), first + words, hipMemcpyDeviceToHost));
     Globals G;
     std::memcpy(&G, buf.data(), sizeof(G));
     const hs_status st = latched(s, G);

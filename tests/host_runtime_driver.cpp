@@ -294,11 +294,29 @@ void first_read()
     }
 }
 
+// No exception leaves a read where the host's memory has run out (they need none).
+void no_memory()
+{
+    Fixture f(3, 40000);
+    std::vector<double> a(8 * 40000);
+    int64_t out[HS_NUM_COUNTERS];
+    double *n = a.data(), *u = n + 40000, *T = u + 3 * 40000, *q = T + 40000;
+    for (int k = 0; k < 2; ++k) {
+        g_no_memory = true;
+        hs_status st = hs_counters(f.sim, 2, out);
+        if (!st) st = hs_sample_moments(f.sim, 1, k, n, u, T, q, nullptr);
+        if (!st) st = hs_sample_moments(f.sim, 1, k, T, n, nullptr, u, nullptr);
+        g_no_memory = false;
+        CHECK(st == HS_OK);
+    }
+}
+
 struct Named {
     const char *name;
     void (*run)();
 };
-const Named kChecks[] = {{"side_stream", side_stream}, {"other_device", other_device}, {"first_read", first_read}};
+const Named kChecks[] = {{"side_stream", side_stream}, {"other_device", other_device}, {"first_read", first_read},
+                         {"no_memory", no_memory}};
 
 }  // namespace
 
