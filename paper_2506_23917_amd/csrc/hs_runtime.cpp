@@ -723,7 +723,6 @@ hs_status copy_out(hs_sim *s, const CopyPart (&part)[N])
     CopyPart held[2][N];                   // pieces on their way through each half, one of a part at most
     int n_held[2] = {0, 0};
     auto drain = [&](int h) -> hipError_t {
-        if (n_held[h] == 0) return hipSuccess;
         const hipError_t e = hipEventSynchronize(s->ev_stage[h]);
         if (e != hipSuccess) return e;
         for (int k = 0; k < n_held[h]; ++k) std::memcpy(held[h][k].to, held[h][k].from, held[h][k].bytes);

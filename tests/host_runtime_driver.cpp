@@ -311,12 +311,23 @@ void no_memory()
     }
 }
 
+// A read waits for its kernel also where no array is asked for.
+void no_arrays()
+{
+    Fixture f(1, 500);
+    for (int k = 0; k < 3; ++k) {
+        int64_t samples = -1;
+        CHECK(hs_sample_moments(f.sim, 0, 0, nullptr, nullptr, nullptr, nullptr, &samples) == HS_OK);
+        CHECK(samples == 0 && !f.main.busy);
+    }
+}
+
 struct Named {
     const char *name;
     void (*run)();
 };
 const Named kChecks[] = {{"side_stream", side_stream}, {"other_device", other_device}, {"first_read", first_read},
-                         {"no_memory", no_memory}};
+                         {"no_memory", no_memory}, {"no_arrays", no_arrays}};
 
 }  // namespace
 

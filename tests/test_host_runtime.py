@@ -22,7 +22,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("name", ["side_stream", "other_device", "first_read", "no_memory"])
+@pytest.mark.parametrize("name", ["side_stream", "other_device", "first_read", "no_memory", "no_arrays"])
 def test_host_runtime(driver, name):
     r = subprocess.run([driver, name], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
