@@ -729,17 +729,28 @@ hs_status copy_out(hs_sim *s, const CopyPart (&part)[N])
         n_held[h] = 0;
         return hipSuccess;
     };
+    // pieces that follow each other on the device go as one copy
+    CopyPart run = {nullptr, nullptr, 0};
+    auto send = [&]() -> hipError_t {
+        const size_t bytes = run.bytes;
+        run.bytes = 0;
+        return bytes ? hipMemcpyAsync(run.to, run.from, bytes, hipMemcpyDeviceToHost, s->stream) : hipSuccess;
+    };
     int h = 0;
     size_t used = 0;
     for (const CopyPart &p : part) {
         for (size_t done = 0; done < p.bytes;) {
             const size_t take = std::min(p.bytes - done, s->stage_half - used);
             char *via = s->stage + h * s->stage_half + used;
-            HIPCHK(s, hipMemcpyAsync(via, (const char *)p.from + done, take, hipMemcpyDeviceToHost, s->stream));
+            const char *from = (const char *)p.from + done;
+            if (run.bytes && (const char *)run.from + run.bytes != from) HIPCHK(s, send());
+            if (!run.bytes) run = {via, from, 0};
+            run.bytes += take;
             held[h][n_held[h]++] = {(char *)p.to + done, via, take};
             done += take;
             used += take;
             if (used == s->stage_half) {
+                HIPCHK(s, send());
                 HIPCHK(s, hipEventRecord(s->ev_stage[h], s->stream));
                 h ^= 1;
                 used = 0;
@@ -747,6 +758,7 @@ hs_status copy_out(hs_sim *s, const CopyPart (&part)[N])
             }
         }
     }
+    HIPCHK(s, send());
     HIPCHK(s, hipEventRecord(s->ev_stage[h], s->stream));
     HIPCHK(s, drain(h ^ 1));
     HIPCHK(s, drain(h));
@@ -1215,18 +1227,12 @@ hs_status hs_sample_moments(hs_sim *s, int c, int mode, double *n, double *u3, d
     if (mode == 0) launch_finalize(s->ctx, s->stream, c, (int)nc, out);
     else launch_moments_now(s->ctx, s->stream, c, (int)nc, out);
     HIPCHK(s, hipGetLastError());
-    // the kernels write the four fields one after the other, each as the caller's array holds it;
-    // arrays that follow each other on the host too are one piece
+    // the kernels write the four fields one after the other, each as the caller's array holds it
     const CopyPart part[4] = {{n, out, n ? 8 * nc : 0},
                               {u3, out + nc, u3 ? 8 * 3 * nc : 0},
                               {T, out + 4 * nc, T ? 8 * nc : 0},
                               {q3, out + 5 * nc, q3 ? 8 * 3 * nc : 0}};
-    if (n && u3 == n + nc && T == n + 4 * nc && q3 == n + 5 * nc) {
-        const CopyPart all[1] = {{n, out, 8 * 8 * nc}};
-        st = copy_out(s, all);
-    } else {
-        st = copy_out(s, part);
-    }
+    st = copy_out(s, part);
     if (st) return st;
     if (n_samples) *n_samples = G.n_samples[c];
     return HS_OK;

@@ -282,9 +282,8 @@ class Sim:
 
     def sample_moments(self, c=0, mode=0) -> dict:
         nc = self.num_cells(c)
-        # one block for the four fields, laid out as the device writes them
-        f = np.empty(8 * nc)
-        n, u, T, q = f[:nc], f[nc:4 * nc].reshape(nc, 3), f[4 * nc:5 * nc], f[5 * nc:].reshape(nc, 3)
+        # arrays of their own: a caller that keeps one field holds that field's memory only
+        n, u, T, q = np.empty(nc), np.empty((nc, 3)), np.empty(nc), np.empty((nc, 3))
         ns = C.c_int64()
         dp = lambda a: a.ctypes.data_as(C.POINTER(C.c_double))
         self._check(self.L.hs_sample_moments(self.h, c, mode, dp(n), dp(u), dp(T), dp(q), C.byref(ns)),
