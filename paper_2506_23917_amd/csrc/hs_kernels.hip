@@ -1471,7 +1471,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(P) ==
         // its cell's start plus the lengths of the cell's runs of lower blocks, found by one lane
         // per run, and its sources follow in order.  Where two runs of a cell share a block
         // (particles that k_move_body took, any other slot order) the tile falls back to
-        // counting: a source's rank among its cell's sources is its place.
+        // counting: a source's rank among its cell's sources is its place.  Runs shorter than 2.5 on
+        // average (flights over many cells) are counted at once: the run placing is a chain of reads as
+        // long as the cell has runs (FP64 kernel on 3072 cells, us by runs and by counting: of 160 particles,
+        // 24 runs 29 and 34, 56 runs 44 and 41, 108 runs 58 and 47, 158 runs 129 and 71; of 60, 10 runs
+        // 15 and 17, 22 runs 19 and 24, 41 runs 26 and 19; of 5 the same).
         // Counting every source against every other took 292 lane-instructions a particle on the
         // 800 x 600 cylinder, the runs 158 (kernel 283 -> 271 us: its loads remain), 64 tubes of
         // 160-particle cells 45 -> 17 us, the FP64 0-D batch (no permutation: no ranks) 39 -> 10.
@@ -1508,17 +1512,19 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(P) ==
             }
             if (lane == 0) run_at[nrun] = (uint16_t)np;
             team_sync<64>();
-            bool tie = false;
-            for (int q = lane; q < nrun; q += 64) {
-                const int at = run_at[q], lc = s_lc[at], e = c_off[lc + 1], blk = s_src[at] >> 6;
-                int to = c_off[lc], a = to;
-                for (int j = c_run[lc]; a < e; ++j) {
-                    const int an = run_at[j + 1], bj = s_src[a] >> 6;
-                    if (bj < blk) to += an - a;
-                    tie = tie || (bj == blk && j != q);
-                    a = an;
+            bool tie = 5 * nrun > 2 * np;
+            if (!tie) {
+                for (int q = lane; q < nrun; q += 64) {
+                    const int at = run_at[q], lc = s_lc[at], e = c_off[lc + 1], blk = s_src[at] >> 6;
+                    int to = c_off[lc], a = to;
+                    for (int j = c_run[lc]; a < e; ++j) {
+                        const int an = run_at[j + 1], bj = s_src[a] >> 6;
+                        if (bj < blk) to += an - a;
+                        tie = tie || (bj == blk && j != q);
+                        a = an;
+                    }
+                    run_by[q] = (int16_t)(to - at);
                 }
-                run_by[q] = (int16_t)(to - at);
             }
             if (!__any(tie)) {
                 team_sync<64>();

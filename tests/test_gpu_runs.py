@@ -62,8 +62,9 @@ def test_order_at_any_number_of_runs(gas, per, width, body, precision):
 
 
 # Kernel times with flights to anywhere against flights within a cell.  The bound lies between what the
-# way for many runs takes (2.7 times as long) and what the placing of runs takes (19).
-@pytest.mark.parametrize("group,nx,ny,per,precision,bound", [("dense", 20, 15, 3850, "fp32", 6.0)])
+# ways for many runs take (2.7 and 3 times as long) and what the placing of runs takes (19 and 5.4).
+@pytest.mark.parametrize("group,nx,ny,per,precision,bound", [("dense", 20, 15, 3850, "fp32", 6.0),
+                                                             ("gather", 64, 48, 160, "fp64", 4.2)])
 def test_many_runs_cost_no_multiple(gas, group, nx, ny, per, precision, bound):
     took = []
     for width in (1.0, 0):
