@@ -3518,13 +3518,15 @@ static int tile_grid(const Ctx &c, int which, long long cap, int parts = 1)
 }
 void Launch::gather(const Ctx &c, void *s)
 {
-    // 8192 blocks fill the chip (eight waves a SIMD).  A batch of many tiles runs on 6144, which
-    // leave the dense kernel beside it a place and end more evenly (800 x 600 cylinder, us a step:
-    // 960 at 8192, 944 at 6144, 942 at 4096); with fewer tiles a block the last round counts for
-    // more (eight jets, 34k tiles of capacity: 196 at 8192, 199 at 6144; 800 x 600 at half the
-    // particles, 52k: 494 and 497; 640 x 480, 63k: 606 and 604)
-    const bool parts = in_parts(c);
-    const int g = tile_grid(c, HS_KERNEL_GATHER, parts ? 2 * kPartTiles2 : max_tiles(c) > 256ll * 256 ? 256ll * 24 : 256ll * 32, parts ? 4 : 1);
+    // 8192 blocks fill the chip (FP32: eight waves a SIMD).  An FP32 batch of many tiles runs on 6144,
+    // which leave the dense kernel beside it a place and end more evenly (us a step at 8192 and 6144: 800 x
+    // 600 cylinder, 97.5k tiles of capacity, 960 and 944, 960 x 720 1114 and 1091, 1200 x 900 at 20 a cell
+    // 1180 and 1155; 120-wide sphere 1113 and 1103, 180-wide 3155 and 3086); with fewer tiles a block the
+    // last round counts for more (eight jets, 34k tiles: 196 and 199; 800 x 600 at half the particles, 52k:
+    // 494 and 497; 640 x 480, 63k: 606 and 604).  FP64 batches, four waves a SIMD, do not gain (800 x 600
+    // cylinder 1473 and 1488, 960 x 720 2012 and 2049, 150-wide sphere 3886 and 3948, 32 jets 1889 and 1927)
+    const bool parts = in_parts(c), many = c.precision != HS_FP64 && max_tiles(c) > 256ll * 256;
+    const int g = tile_grid(c, HS_KERNEL_GATHER, parts ? 2 * kPartTiles2 : many ? 256ll * 24 : 256ll * 32, parts ? 4 : 1);
     const dim3 grid(g), block(64);
     if (c.precision == HS_FP64) {
         if (parts) hipLaunchKernelGGL((k_sort_gather<double, kTileW, kCapWave, true>), grid, block, 0, S_(s), c);
