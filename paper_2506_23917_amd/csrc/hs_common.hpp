@@ -28,7 +28,7 @@ constexpr int kBlock = 256;          // threads per block of the streaming kerne
 // Size classes of the block-per-cell collide kernel (cells above the tile kernel's limit):
 // class 0 up to kCapBlockMid particles, 1 up to kCapBlockMax, 2 up to kCapBlockLds (the
 // densest worked on in LDS), 3 above.  Each class has its own list of cells, built by the
-// scan, so a launch for one class visits only its own cells.
+// scatter launch, so a launch for one class visits only its own cells.
 constexpr int kCapBlockMid = 512;
 constexpr int kCapBlockMax = 2048;   // powers of two: the bitonic sort pads to one
 constexpr int kCapBlockLds = 4096;

@@ -1,16 +1,19 @@
 // hs_kernels.hip -- gfx950 kernels of one step of the hybrid SP-Shakhov / DSMC particle
 // update (arXiv 2506.23917, Sec. 3.2 Steps 1-5) and their launchers.
 //
-// Step pipeline (all on one stream, fixed launch arguments):
+// Step pipeline (fixed launch arguments; everything on the sim's stream but the dense kernels, which
+// run on its side stream between the scatter and finish_step):
 //   inject_count / inject_scan / inject_fill   inflow faces -> new particles appended
-//   move_count     per particle: free flight + walls -> new cell, atomic per-cell slot
-//   scan_*         exclusive scan of the cell counts -> cell_start, dense-cell list
-//   scatter        perm[cell_start[c] + slot] = source index
-//   collide_wave   one wavefront per cell (<= cap_wave particles): gather the cell's
-//                  sources, restore their array order, re-run their move, write the new
-//                  sorted state; moments, split, NTC chain, Shakhov, rescale, sampling
-//   collide_block  the same with a 256-thread block for each dense cell
-//   finish_step    live count, step counter, sample counters
+//   move_fast / move_mesh / move_body          per particle: free flight + walls -> new cell, atomic
+//                    per-cell slot (grid cases; mesh cases; particles near a body)
+//   scan_reduce / scan_final                   exclusive scan of the cell counts -> cell starts
+//   scatter          perm[cell start + slot] = source index; its first blocks build the tile table,
+//                    clear the counts and list the dense cells
+//   sort_gather      per tile (a wave): stable order of each cell's sources, sorted state written
+//   cell_scalars     per tile: moments, timescales and split, N_col; one record a cell
+//   collide_tile / collide_parts   per tile (or part of one): NTC, Shakhov, rescale, sampling
+//   collide_dense    a block per dense cell (> cap_wave particles): all of the last three
+//   finish_step      live count, step counter, sample counters
 #include "hs_device.hpp"
 
 #include <mutex>
@@ -545,7 +548,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_reduce(Ctx C)
     if (threadIdx.x == 0) C.scan_part[blockIdx.x] = total;
 }
 
-// (The counts are cleared by k_tile_table: other blocks read them here.)
+// (The counts are cleared with the tile table, by the next launch: other blocks read them here.)
 __global__ __launch_bounds__(kBlock) void k_scan_final(Ctx C, int direct)
 {
     if (C.g->halt) return;
@@ -1633,17 +1636,6 @@ __device__ __forceinline__ void group_sum(double (&x)[K], int kb)
 #pragma unroll
         for (int k = 0; k < K; ++k) x[k] = row_pair_sum<32>(x[k]);
     }
-}
-
-__device__ __forceinline__ int group_sum_i(int x, int kb)
-{
-    if (kb >= 1) x += dpp_partner_i<kDppXor1>(x);
-    if (kb >= 2) x += dpp_partner_i<kDppXor2>(x);
-    if (kb >= 3) x += dpp_partner_i<kDppHalfMirror>(x);
-    if (kb >= 4) x += dpp_partner_i<kDppMirror>(x);
-    if (kb >= 5) { const PairI p = row_pair<16>(x); x = p.a + p.b; }
-    if (kb >= 6) { const PairI p = row_pair<32>(x); x = p.a + p.b; }
-    return x;
 }
 
 // The same with a group size per lane (groups of several sizes in one wave, each aligned to
@@ -3310,7 +3302,7 @@ __global__ void k_finish_step(Ctx C, int sorted)
     if (threadIdx.x == 0) {
         if (sorted) {
             G->n_live = G->n_new;
-            for (int k = 0; k < kDenseClasses; ++k) G->n_big[k] = 0;   // rebuilt by the next step's scan
+            for (int k = 0; k < kDenseClasses; ++k) G->n_big[k] = 0;   // listed again by the next step's scatter launch
         }
         G->n_work = 0;
         G->n_total = G->n_live;
