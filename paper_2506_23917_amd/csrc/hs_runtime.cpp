@@ -680,7 +680,7 @@ hs_status read_globals(hs_sim *s, Globals &G)
 
 // Most bytes of one half of the staging memory.  A sim may be read only once, and page-locking more than
 // a megabyte costs more than that read gains; smaller halves cost the reads after it.  First and later
-// reads of hs_sample_moments (us): 10,080 cells 460 and 90 at 4 MB a half, 150
+// reads of hs_sample_moments (us, into one block of memory): 10,080 cells 460 and 90 at 4 MB a half, 150
 // and 91 at 448 KB, 164 and 102 at 256 KB (355 and 350 without staging); 82,668 cells 2270 and 310, 356 and
 // 352, 470 and 465 (2250 and 730); 480,000 cells 2760 and 1310, 1615 and 1600, 2350 and 2320 (5900 and 4430).
 constexpr size_t kStageHalf = (size_t)448 << 10;
@@ -754,14 +754,17 @@ hs_status copy_out(hs_sim *s, const CopyPart (&part)[N])
                 HIPCHK(s, hipEventRecord(s->ev_stage[h], s->stream));
                 h ^= 1;
                 used = 0;
-                HIPCHK(s, drain(h));
+                if (n_held[h]) HIPCHK(s, drain(h));
             }
         }
     }
-    HIPCHK(s, send());
-    HIPCHK(s, hipEventRecord(s->ev_stage[h], s->stream));
-    HIPCHK(s, drain(h ^ 1));
-    HIPCHK(s, drain(h));
+    if (used) {
+        HIPCHK(s, send());
+        HIPCHK(s, hipEventRecord(s->ev_stage[h], s->stream));
+    }
+    if (!n_held[0] && !n_held[1]) HIPCHK(s, hipStreamSynchronize(s->stream));   // no array was asked for
+    if (n_held[h ^ 1]) HIPCHK(s, drain(h ^ 1));
+    if (n_held[h]) HIPCHK(s, drain(h));
     return HS_OK;
 }
 
