@@ -2803,11 +2803,11 @@ __global__ __launch_bounds__(NB) __attribute__((amdgpu_waves_per_eu(sizeof(P) ==
         // are sorted bitonically.  (Three O-grids, 330 particles a cell: step 445 us with a search of
         // all runs for every source, 406 so and with the draw queue below.)
         // The placing compares each run with each other one, so cells of many runs (particles from all
-        // over the domain, few of a block) are sorted too: above 16 sqrt(p2) runs, p2 the size the sort
-        // pads to (FP32 kernel on 300 cells, us by runs and by the sort: of 2700 particles, 680 runs 459
-        // and 821, 1441 runs 1379 and 848, 2434 runs 3492 and 864; of 950, 240 runs 44 and 85, 684 runs 98
-        // and 87).  In a case with a body on the grid, where the placing may find a shared block and be
-        // in vain, above half as many, a quarter of the sort's time.
+        // over the domain, few of a block) are sorted too: above 16 sqrt(n) runs, where the two cost about
+        // the same (FP32 kernel on 300 cells, us by runs and by the sort: of 2700 particles, 680 runs 459
+        // and 821, 1441 runs 1379 and 848, 2434 runs 3492 and 864; of 950, 240 runs 44 and 85, 509 runs 79
+        // and 89, 684 runs 98 and 87).  In a case with a body on the grid, where the placing may find a
+        // shared block and be in vain, above half as many, a quarter of the sort's time.
         if constexpr (!GLOB) {
             for (int k = tid; k < n; k += NB) s_src[k] = use_perm ? C.perm[s0 + k] : s0 + k;
             __syncthreads();
@@ -2831,37 +2831,31 @@ __global__ __launch_bounds__(NB) __attribute__((amdgpu_waves_per_eu(sizeof(P) ==
                 const int rows = lane < nrow ? s_rows[lane] : 0;
                 const int upto = wave_incl_scan(rows);
                 const int nrun = wave_last(upto);
-                int p2 = 4;
-                while (p2 < n) p2 <<= 1;
-                bool sort = nrun * nrun > (cs.body && !cs.mesh ? 64 : 256) * p2;
-                if (!sort) {
-                    for (int r = tid >> 6; r < nrow; r += NB / 64) {
-                        const int k = 64 * r + lane;
-                        const bool h = run_head(k);
-                        const unsigned long long m = __ballot(h);
-                        if (h) at[__builtin_amdgcn_readlane(upto - rows, r) + __popcll(m & ((1ull << lane) - 1ull))] = k;
-                    }
-                    __syncthreads();
-                    for (int q = tid; q < ((nrun + 3) & ~3); q += NB) {
-                        len[q] = q < nrun ? (q + 1 < nrun ? at[q + 1] : n) - at[q] : 0;
-                        blk[q] = q < nrun ? s_src[at[q]] >> 6 : 0x7fffffff;
-                    }
-                    __syncthreads();
-                    bool tie = false;
-                    for (int q = tid; q < nrun; q += NB) {
-                        const int mine = blk[q];
-                        int to = 0, same = 0;
-                        for (int j = 0; j < nrun; j += 4) {
-                            const int4 b4 = *reinterpret_cast<const int4 *>(&blk[j]), l4 = *reinterpret_cast<const int4 *>(&len[j]);
-                            to += (b4.x < mine ? l4.x : 0) + (b4.y < mine ? l4.y : 0) + (b4.z < mine ? l4.z : 0) + (b4.w < mine ? l4.w : 0);
-                            same += (int)(b4.x == mine) + (int)(b4.y == mine) + (int)(b4.z == mine) + (int)(b4.w == mine);
-                        }
-                        tie = tie || same > 1;
-                        at[q] = to - at[q];
-                    }
-                    sort = __syncthreads_or(tie) != 0;
+                for (int r = tid >> 6; r < nrow; r += NB / 64) {
+                    const int k = 64 * r + lane;
+                    const bool h = run_head(k);
+                    const unsigned long long m = __ballot(h);
+                    if (h) at[__builtin_amdgcn_readlane(upto - rows, r) + __popcll(m & ((1ull << lane) - 1ull))] = k;
                 }
-                if (!sort) {
+                __syncthreads();
+                for (int q = tid; q < ((nrun + 3) & ~3); q += NB) {
+                    len[q] = q < nrun ? (q + 1 < nrun ? at[q + 1] : n) - at[q] : 0;
+                    blk[q] = q < nrun ? s_src[at[q]] >> 6 : 0x7fffffff;
+                }
+                __syncthreads();
+                bool tie = nrun * nrun > (cs.body && !cs.mesh ? 64 : 256) * n;
+                for (int q = tid; q < (tie ? 0 : nrun); q += NB) {
+                    const int mine = blk[q];
+                    int to = 0, same = 0;
+                    for (int j = 0; j < nrun; j += 4) {
+                        const int4 b4 = *reinterpret_cast<const int4 *>(&blk[j]), l4 = *reinterpret_cast<const int4 *>(&len[j]);
+                        to += (b4.x < mine ? l4.x : 0) + (b4.y < mine ? l4.y : 0) + (b4.z < mine ? l4.z : 0) + (b4.w < mine ? l4.w : 0);
+                        same += (int)(b4.x == mine) + (int)(b4.y == mine) + (int)(b4.z == mine) + (int)(b4.w == mine);
+                    }
+                    tie = tie || same > 1;
+                    at[q] = to - at[q];
+                }
+                if (!__syncthreads_or(tie)) {
                     int32_t *out = len;
                     for (int r = tid >> 6; r < nrow; r += NB / 64) {
                         const int k = 64 * r + lane;
@@ -2872,6 +2866,8 @@ __global__ __launch_bounds__(NB) __attribute__((amdgpu_waves_per_eu(sizeof(P) ==
                     __syncthreads();
                     for (int k = tid; k < n; k += NB) s_src[k] = out[k];
                 } else {
+                    int p2 = 4;
+                    while (p2 < n) p2 <<= 1;
                     for (int k = n + tid; k < p2; k += NB) s_src[k] = 0x7fffffff;
                     __syncthreads();
                     bitonic_sort<NB>(s_src, p2, tid);
